@@ -281,7 +281,7 @@ int frog_search_noalloc(const frog_index_t* idx, const float* d_queries, int64_t
  * of its range with the exact distance.  Every row is exact.  1 <= k <= 256.
  * d_certified (NULL or nq int32) tells how each row was obtained: 1 = by the
  * margin test (or an empty range), 2 = by the exhaustive exact pass.  The
- * ranges and the certification are read back to the host, so this call
+ * queries left to that pass are read back to the host, so this call
  * synchronises `stream`; it is a ground-truth tool, not the search path. */
 int frog_bruteforce_filtered(const frog_index_t* idx, const float* d_queries, int64_t nq,
                              const double* d_lo, const double* d_hi, int k,

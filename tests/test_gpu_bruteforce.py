@@ -101,3 +101,43 @@ def test_bruteforce_uncertified_rows_are_exact(k):
     ids, ds, cert, o_ids, o_d = _run(X, attr, Q, lo, hi, k)
     assert np.isin(cert, (1, 2)).all() and (cert == 2).sum() >= nq // 2
     assert_parity(ids, ds, o_ids, o_d, max_residual=0)
+
+
+@pytest.mark.parametrize("n,d,nq,k", [(1, 5, 3, 4), (15, 32, 33, 10), (257, 33, 1, 33), (1536, 64, 32, 64), (1537, 96, 31, 65),
+                                      (24575, 20, 70, 10), (24576, 128, 65, 129), (24592, 130, 17, 1), (393216, 16, 40, 10)])
+def test_bruteforce_sampling_passes(n, d, nq, k):
+    # sizes around those at which a further sampling pass is added (1,536 and
+    # 24,576 and 393,216 rows at k <= 64; half a tile, a tile and a bit more
+    # of queries; every number of list entries re-ranked; both row paths)
+    print(f"[gpu] bruteforce passes n={n} d={d} nq={nq} k={k}", flush=True)
+    rng = np.random.default_rng(n + d)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    attr = rng.permutation(n).astype(np.float64)
+    Q = rng.standard_normal((nq, d)).astype(np.float32)
+    lo, hi = workloads.ranges_for_selectivity(rng, np.exp2(-8.0 * rng.random(nq)), n)
+    lo[0], hi[0] = 0, n - 1
+    ids, ds, cert, o_ids, o_d = _run(X, attr, Q, lo, hi, k)
+    assert (cert == 1).all()
+    assert_parity(ids, ds, o_ids, o_d, max_residual=0)
+
+
+@pytest.mark.parametrize("near", [False, True])
+def test_bruteforce_misleading_sample(near):
+    # the rows of the sampled blocks (every 16th block of 16 ranks) lie all
+    # nearer to the queries than the others, or all farther: then the
+    # threshold they give lets every other row into the list, which
+    # overflows, and the exact pass has to give the result
+    print(f"[gpu] bruteforce, sampled rows nearer={near}", flush=True)
+    rng = np.random.default_rng(5)
+    n, d, nq, k = 20000, 24, 40, 10
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    sampled = (np.arange(n) // 16) % 16 == 0
+    X[sampled != near] += 6.0      # the others, or the sampled ones, far away
+    attr = np.arange(n, dtype=np.float64)
+    Q = rng.standard_normal((nq, d)).astype(np.float32)
+    cnt = np.array([n, 12000, 300, 40] * (nq // 4))
+    lo = rng.integers(0, n - cnt + 1).astype(np.float64)
+    hi = lo + cnt - 1
+    ids, ds, cert, o_ids, o_d = _run(X, attr, Q, lo, hi, k)
+    assert np.isin(cert, (1, 2)).all()
+    assert_parity(ids, ds, o_ids, o_d, max_residual=0)
