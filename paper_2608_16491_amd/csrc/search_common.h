@@ -770,7 +770,11 @@ __device__ void traverse(const DevIndex& ix, const SearchLaunch& A, int64_t gvis
     int32_t st[FROG_STAT_N];
 #pragma unroll
     for (int i = 0; i < FROG_STAT_N; ++i) st[i] = 0;
-    if (Q.ne > 0) {
+    // When every rank of the range is an entry point, every candidate is
+    // visited from the start: no expansion evaluates anything and the pool is
+    // the result as it stands.  (The statistics count the expansions, so only
+    // the lean instance leaves them out.)
+    if (Q.ne > 0 && !(LEAN && Q.all)) {
     st[FROG_STAT_ENTRY] = (int32_t)Q.ne;
     st[FROG_STAT_DIST] = (int32_t)Q.ne;
 
