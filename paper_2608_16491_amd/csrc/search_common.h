@@ -27,8 +27,9 @@
 //     hash_log2 = 0 selects an exact per-wave bitmap in device memory instead
 //     (used to count distinct evaluations);
 //   - distances: each vector is read by 8 lanes as 16-byte loads (128
-//     contiguous bytes per load instruction and vector), differences and
-//     squares in double, an 8-lane butterfly sum, one rounding to float --
+//     contiguous bytes per load instruction and vector), differences in
+//     double, their squares added by double fused multiply-adds, an 8-lane
+//     butterfly sum, one rounding to float --
 //     the library's canonical squared L2.  d > 128 uses all 64 lanes per
 //     vector, a per-lane sum over its chunks and a 64-lane sum.  No matrix
 //     cores: every gathered vector is used once;
@@ -317,10 +318,10 @@ __device__ float eval_small(const XT* __restrict__ X, int dp, const float4 (&qv)
             asm volatile("" : "+v"(qf.x), "+v"(qf.y), "+v"(qf.z), "+v"(qf.w));
             const double q0 = qf.x, q1 = qf.y, q2 = qf.z, q3 = qf.w;
             double t;
-            t = q0 - (double)x[c].x; s += t * t;
-            t = q1 - (double)x[c].y; s += t * t;
-            t = q2 - (double)x[c].z; s += t * t;
-            t = q3 - (double)x[c].w; s += t * t;
+            t = q0 - (double)x[c].x; s = __builtin_fma(t, t, s);
+            t = q1 - (double)x[c].y; s = __builtin_fma(t, t, s);
+            t = q2 - (double)x[c].z; s = __builtin_fma(t, t, s);
+            t = q3 - (double)x[c].w; s = __builtin_fma(t, t, s);
         }
         s = sum8(s);
         // vector sb0 + g sits in lanes 8g..8g+7; lane sb0 + g takes it
@@ -328,6 +329,29 @@ __device__ float eval_small(const XT* __restrict__ X, int dp, const float4 (&qv)
         if ((lane >> 3) == ((sb0 >> 3) & 7)) mine = got;
     }
     return mine;
+}
+
+// The same for one step: the group of 8 lanes reads vector `id` (the same in
+// its lanes) and all of them receive its distance.
+// KEEP: the query stays in fp32 registers and is widened on each use, else
+// the compiler may hold it widened across the caller's loop.
+template <int C, bool KEEP, typename XT = float>
+__device__ __forceinline__ float eval_group8(const XT* __restrict__ X, int dp, const float4 (&qv)[C], int32_t id) {
+    float4 x[C];
+    load_row<C, XT>(X, dp, id, lane_id() & 7, true, x);
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        float4 qf = qv[c];
+        if constexpr (KEEP) asm volatile("" : "+v"(qf.x), "+v"(qf.y), "+v"(qf.z), "+v"(qf.w));
+        const double q0 = qf.x, q1 = qf.y, q2 = qf.z, q3 = qf.w;
+        double t;
+        t = q0 - (double)x[c].x; s = __builtin_fma(t, t, s);
+        t = q1 - (double)x[c].y; s = __builtin_fma(t, t, s);
+        t = q2 - (double)x[c].z; s = __builtin_fma(t, t, s);
+        t = q3 - (double)x[c].w; s = __builtin_fma(t, t, s);
+    }
+    return (float)sum8(s);
 }
 
 // Same result as eval_small for the entry-point batches (1..64 candidates),
@@ -357,10 +381,10 @@ struct Gather16 {
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 double t;
-                t = q0 - (double)x[g][c].x; s[g] += t * t;
-                t = q1 - (double)x[g][c].y; s[g] += t * t;
-                t = q2 - (double)x[g][c].z; s[g] += t * t;
-                t = q3 - (double)x[g][c].w; s[g] += t * t;
+                t = q0 - (double)x[g][c].x; s[g] = __builtin_fma(t, t, s[g]);
+                t = q1 - (double)x[g][c].y; s[g] = __builtin_fma(t, t, s[g]);
+                t = q2 - (double)x[g][c].z; s[g] = __builtin_fma(t, t, s[g]);
+                t = q3 - (double)x[g][c].w; s[g] = __builtin_fma(t, t, s[g]);
             }
         }
         const int src = (lane & 7) << 3;
@@ -446,10 +470,10 @@ __device__ float eval_large(const float* __restrict__ X, int dp, const float* __
                 asm volatile("" : "+v"(qf.x), "+v"(qf.y), "+v"(qf.z), "+v"(qf.w));
                 const double q0 = qf.x, q1 = qf.y, q2 = qf.z, q3 = qf.w;
                 double t, u = 0.0;
-                t = q0 - (double)x[i].x; u += t * t;
-                t = q1 - (double)x[i].y; u += t * t;
-                t = q2 - (double)x[i].z; u += t * t;
-                t = q3 - (double)x[i].w; u += t * t;
+                t = q0 - (double)x[i].x; u = __builtin_fma(t, t, u);
+                t = q1 - (double)x[i].y; u = __builtin_fma(t, t, u);
+                t = q2 - (double)x[i].z; u = __builtin_fma(t, t, u);
+                t = q3 - (double)x[i].w; u = __builtin_fma(t, t, u);
                 s += in ? u : 0.0;
             }
             return s;
@@ -486,10 +510,10 @@ __device__ float eval_large(const float* __restrict__ X, int dp, const float* __
             const double q0 = b < d ? q[b] : 0.f, q1 = b + 1 < d ? q[b + 1] : 0.f;
             const double q2 = b + 2 < d ? q[b + 2] : 0.f, q3 = b + 3 < d ? q[b + 3] : 0.f;
             double t, u = 0.0;
-            t = q0 - (double)x.x; u += t * t;
-            t = q1 - (double)x.y; u += t * t;
-            t = q2 - (double)x.z; u += t * t;
-            t = q3 - (double)x.w; u += t * t;
+            t = q0 - (double)x.x; u = __builtin_fma(t, t, u);
+            t = q1 - (double)x.y; u = __builtin_fma(t, t, u);
+            t = q2 - (double)x.z; u = __builtin_fma(t, t, u);
+            t = q3 - (double)x.w; u = __builtin_fma(t, t, u);
             s += u;
         }
         s = sum64(s);
@@ -726,6 +750,13 @@ struct QueryCtx {
         if constexpr (C > 0) return eval_small<C, XT>(rows_of<XT>(ix), ix.dp, qv, nb, myid);
         else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, myid);
     }
+    // one step of the lean traversal: C > 0 the group's vector, else lane j's
+    // candidate j < nb
+    template <bool KEEP>
+    __device__ __forceinline__ float eval_groups(const DevIndex& ix, int nb, int32_t id) const {
+        if constexpr (C > 0) return eval_group8<C, KEEP, XT>(rows_of<XT>(ix), ix.dp, qv, id);
+        else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, id);
+    }
     __device__ float eval_batch(const DevIndex& ix, int nb, int32_t myid) const {
         if constexpr (C > 0) return eval_pipelined<C, XT>(rows_of<XT>(ix), ix.dp, qv, nb, myid);
         else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, myid);
@@ -751,30 +782,213 @@ __device__ void entry_chunk(const DevIndex& ix, const SearchLaunch& A, const Que
     }
 }
 
+// a11: output, rank -> original id, padding
+template <int LP>
+__device__ void write_results(const DevIndex& ix, const SearchLaunch& A, int64_t qi, const uint64_t (&key)[LP], int np) {
+    const int lane = lane_id();
+    const int k = A.k;
+#pragma unroll
+    for (int s = 0; s < LP; ++s) {
+        const int p = s * 64 + lane;
+        if (p < k) {
+            int32_t oid = -1;
+            float od = __int_as_float(0x7f800000);
+            if (p < np) {
+                oid = ix.perm[(uint32_t)key[s]];
+                od = __uint_as_float((uint32_t)(key[s] >> 32));
+            }
+            A.ids[qi * k + p] = oid;
+            A.dists[qi * k + p] = od;
+        }
+    }
+}
+
+// The key at a (wave-uniform) position.
+template <int LP>
+__device__ __forceinline__ uint64_t key_at(const uint64_t (&key)[LP], int p) {
+    uint64_t k = 0;
+#pragma unroll
+    for (int s = 0; s < LP; ++s)
+        if (LP == 1 || s == (p >> 6)) k = readlane64(key[s], p & 63);
+    return k;
+}
+// Insert kj into the sorted keys (np of them, at most L kept): the keys above
+// it move up one lane (a wavefront shift by data-parallel primitives; lane 0
+// of a register takes lane 63 of the one below), and so do the open bits (one
+// per pool entry: not expanded yet), which are wave-uniform.  A key already
+// there, or at or beyond the L-th of a full pool, is dropped.  Keys pushed
+// out stay in the lanes from L on: they are above every key a later insertion
+// counts.
+template <int LP>
+__device__ __forceinline__ void insert_key(uint64_t (&key)[LP], uint64_t (&open)[LP], int& np, int L, uint64_t kj) {
+    const int lane = lane_id();
+    int c = 0;
+#pragma unroll
+    for (int s = 0; s < LP; ++s) c += __popcll(ballot(key[s] < kj));
+    if (c >= L) return;
+    const int cs = c >> 6, cl = c & 63;
+    if (key_at<LP>(key, c) == kj) return;
+#pragma unroll
+    for (int s = LP - 1; s >= 0; --s) {
+        if (s < cs) continue;
+        // lane 0 of the shifted register (used only above register cs)
+        const uint64_t in = s > 0 ? readlane64(key[s > 0 ? s - 1 : 0], 63) : kj;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)in, (int)(uint32_t)key[s], 0x138, 0xF, 0xF, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(in >> 32), (int)(uint32_t)(key[s] >> 32), 0x138, 0xF, 0xF, false);
+        const uint64_t up = ((uint64_t)hi << 32) | lo;
+        if (s > cs) {
+            key[s] = up;
+            open[s] = (open[s] << 1) | (open[s > 0 ? s - 1 : 0] >> 63);
+        } else {
+            key[s] = lane < cl ? key[s] : (lane == cl ? kj : up);
+            const uint64_t below = ((uint64_t)1 << cl) - 1;
+            open[s] = (open[s] & below) | ((open[s] & ~below) << 1) | ((uint64_t)1 << cl);
+        }
+    }
+    np = np + 1 < L ? np + 1 : L;
+}
+
+// The bits of register s's pool entries below L.
+__device__ __forceinline__ uint64_t slot_mask(int L, int s) {
+    const int left = L - 64 * s;
+    return left >= 64 ? ~0ull : (left <= 0 ? 0ull : ((uint64_t)1 << left) - 1);
+}
+
+// The best-first loop of Alg. 2 in the timed configuration (no statistics,
+// lazy check, LDS visited table): the same trajectory as traverse().  What
+// bounds it is the chain of dependent steps per expansion, so the steps
+// between the two memory reads of an expansion (candidate rows, vectors) are
+// kept few: one ballot admits the first B in-range entries where they lie,
+// one pass through LDS hands the fresh ones to their groups of 8 lanes (C >
+// 0), and their keys are inserted into the pool from the lanes that computed
+// them, by wavefront shifts.  With the entries compacted twice, the distances
+// moved to the candidates' lanes and the pool merged by scattering it through
+// LDS, an expansion took five more trips through LDS.  One query alone
+// (100k x 128, L = 64): 128 us per call before, 119 us so, 109 us with the
+// squares added by fused multiply-adds and the query held in double (pools of
+// at most 64; a distance then takes 3 vector instructions per dimension and
+// lane instead of 5, all of the same rate).
+template <int C, int LP, typename XT>
+__device__ void traverse_lean(const DevIndex& ix, const SearchLaunch& A, const QueryCtx<C, XT>& Q, Pool<LP>& pool,
+                              const WaveLds<LP>& W, const Visited& vis) {
+    const int lane = lane_id();
+    // When every rank of the range is an entry point, every candidate is
+    // visited from the start: no expansion evaluates anything and the pool is
+    // the result as it stands.
+    if (Q.ne > 0 && !Q.all) {
+        const int H = ix.H, m = ix.m, B = A.B, L = A.L;
+        const int32_t l32 = (int32_t)Q.l, r32 = (int32_t)Q.r;   // ranks fit int32
+        int Ls, Le;
+        hotspot(Q.l, Q.r, H, ix.n, Ls, Le);
+        Ls = uniform(Ls);
+        Le = uniform(Le);
+        if (A.hotspot_mode == 1) Le = H - 1;                   // ablation: no end condition
+        if (A.hotspot_mode == 2) { Ls = 0; Le = H - 1; }       // ablation: no localisation
+        const int T = 1 << A.hash_log2;
+        for (int i = lane; i < T; i += 64) vis.tab[i] = -1;
+        wave_sync();
+        uint64_t open[LP];
+#pragma unroll
+        for (int s = 0; s < LP; ++s) {
+            if (s * 64 + lane < pool.np) vis.insert((int32_t)(uint32_t)pool.key[s]);
+            open[s] = slot_mask(pool.np, s);
+        }
+        wave_sync();
+        const int nent = (Le - Ls + 1) * m;
+        int32_t pre_u = -1, pre_v = -1;
+        for (;;) {
+            // a4: the first open entry, and the one after it (the prefetch's
+            // guess at the next selection)
+            int32_t u = -1, nu = -1;
+#pragma unroll
+            for (int s = 0; s < LP; ++s) {
+                uint64_t mk = open[s];
+                if (u < 0 && mk != 0) {
+                    u = __builtin_amdgcn_readlane((int32_t)(uint32_t)pool.key[s], __builtin_ctzll(mk));
+                    mk &= mk - 1;
+                    open[s] = mk;
+                }
+                if (nu < 0 && u >= 0 && mk != 0)
+                    nu = __builtin_amdgcn_readlane((int32_t)(uint32_t)pool.key[s], __builtin_ctzll(mk));
+            }
+            if (u < 0) break;
+            // a5: the hotspot's candidates.  The slice's first 64 entries
+            // (loaded on a miss) are issued before the prefetch, and the
+            // prefetch is issued on every hop (a valid row when there is no
+            // guess) with every lane active, its lanes past the slice masked
+            // where it is used: the loads in flight are then the same on every
+            // path, and waiting for the slice leaves the prefetch in flight
+            // (the wait counter retires loads in order; an optional load makes
+            // the wait drain them all).  The previous prefetch is not read
+            // after the next one is issued, so the two share a register.
+            const int32_t* row = ix.ENC + ((int64_t)u * H + Ls) * m;
+            const int lidx = lane < nent ? lane : 0;
+            int32_t x = pre_v;
+            if (u != pre_u) x = row[lidx];
+            pre_u = nu;
+            pre_v = ix.ENC[((int64_t)(nu >= 0 ? nu : u) * H + Ls) * m + lidx];
+            int32_t v = lane < nent ? x : -1;
+            // a6, a7: the first B in-range entries in stored order, 64 at a
+            // time; those not visited are evaluated and merged.  (Merging the
+            // slices one after the other leaves the same L smallest keys as
+            // merging them at once.)
+            int want = B;
+            for (int off = 0;;) {
+                const bool inr = v >= l32 && v <= r32;
+                const uint64_t pm = ballot(inr);
+                // the table is read in every lane, beside the sample test
+                const uint32_t slot = vis.slot(v);
+                const int32_t seen = vis.tab[slot];
+                bool fresh = inr && mbcnt(pm) < want && seen != v;
+                if (Q.shared) fresh = fresh && !((uint32_t)(splitmix64(Q.pkey ^ (uint64_t)(uint32_t)v) >> 32) < Q.T);
+                if (fresh) vis.tab[slot] = v;
+                const uint64_t fm = ballot(fresh);
+                const int ns = __popcll(fm);
+                if (ns > 0) {
+                    if (fresh) W.enbuf[mbcnt(fm)] = v;
+                    wave_sync();
+                    constexpr int G = C > 0 ? 8 : 64;   // candidates per step
+                    for (int j0 = 0; j0 < ns; j0 += G) {
+                        const int j = C > 0 ? j0 + (lane >> 3) : lane;
+                        const int32_t id = W.enbuf[j < ns ? j : ns - 1];
+                        // a8
+                        const float dd = Q.template eval_groups<(LP > 1)>(ix, ns, id);
+                        // a9 + a10: MergeTopEfS
+                        const uint64_t nkey = make_key(dd, id);
+                        bool cand = j < ns && (C == 0 || (lane & 7) == 0);
+                        if (pool.np >= L) cand = cand && nkey < key_at<LP>(pool.key, L - 1);
+                        for (uint64_t mm = ballot(cand); mm; mm &= mm - 1)
+                            insert_key<LP>(pool.key, open, pool.np, L, readlane64(nkey, __builtin_ctzll(mm)));
+                    }
+#pragma unroll
+                    for (int s = 0; s < LP; ++s) open[s] &= slot_mask(L, s);
+                    wave_sync();   // the list is read before the next one is written
+                }
+                want -= __popcll(pm);
+                off += 64;
+                if (off >= nent || want <= 0) break;
+                const int e = off + lane;
+                v = e < nent ? row[e] : -1;
+            }
+        }
+    }
+    write_results<LP>(ix, A, Q.qi, pool.key, pool.np);
+}
+
 // a2, a4-a11 for one query whose pool holds the L nearest entry points:
 // HotspotLocalization, the best-first loop of Alg. 2, output and statistics.
-// LEAN: the timed configuration (no statistics, lazy check, LDS visited
-// table), with the statistics and the ablation branches compiled out and the
-// EN list compacted by lane permutes whenever the slice's first 64 entries
-// hold it (almost always: the budget fills within about 40 entries at the
-// bench settings); the trajectory is the same.
-template <int C, int LP, typename XT, bool LEAN = false>
+template <int C, int LP, typename XT>
 __device__ void traverse(const DevIndex& ix, const SearchLaunch& A, int64_t gvis_words, const QueryCtx<C, XT>& Q,
                          Pool<LP>& pool, const WaveLds<LP>& W, const Visited& vis) {
     const int lane = lane_id();
     const int T = A.hash_log2 > 0 ? (1 << A.hash_log2) : 0;
-    const int H = ix.H, m = ix.m, B = A.B, L = A.L, k = A.k;
+    const int H = ix.H, m = ix.m, B = A.B, L = A.L;
     const int64_t qi = Q.qi, l = Q.l, r = Q.r;
-    const int32_t l32 = (int32_t)l, r32 = (int32_t)r;   // ranks fit int32
-    const bool eager = !LEAN && A.eager;
+    const bool eager = A.eager;
     int32_t st[FROG_STAT_N];
 #pragma unroll
     for (int i = 0; i < FROG_STAT_N; ++i) st[i] = 0;
-    // When every rank of the range is an entry point, every candidate is
-    // visited from the start: no expansion evaluates anything and the pool is
-    // the result as it stands.  (The statistics count the expansions, so only
-    // the lean instance leaves them out.)
-    if (Q.ne > 0 && !(LEAN && Q.all)) {
+    if (Q.ne > 0) {
     st[FROG_STAT_ENTRY] = (int32_t)Q.ne;
     st[FROG_STAT_DIST] = (int32_t)Q.ne;
 
@@ -866,31 +1080,6 @@ __device__ void traverse(const DevIndex& ix, const SearchLaunch& A, int64_t gvis
         pre_v = ix.ENC[((int64_t)(nu >= 0 ? nu : u) * H + Ls) * m + lidx];
         if (nu >= 0) st[FROG_STAT_LOADED] += (int32_t)(nent < 64 ? nent : 64);
         const int32_t v0 = lane < nent ? x : -1;
-        if (LEAN) {
-            // the first 64 entries of the hotspot slice (the prefetched ones
-            // on a hit); when they hold the whole slice or at least B
-            // in-range entries, the EN list of Alg. 4 (the first B in-range
-            // entries in stored order) lies in them: admit those, move them
-            // to lanes 0.., check them against the visited table (lazy
-            // check) and move the fresh ones down.  Otherwise the general
-            // path below scans on.
-            const bool inr = v0 >= l32 && v0 <= r32;
-            const uint64_t pm = ballot(inr);
-            const int tot = __popcll(pm);
-            if (nent <= 64 || tot >= B) {
-                const int nen = tot < B ? tot : B;
-                const uint64_t am = ballot(inr && mbcnt(pm) < nen);
-                const int32_t v = compact_lanes(v0, am);
-                const bool fresh = lane < nen && !Q.is_entry(v) && vis.check_insert(v);
-                const uint64_t fm = ballot(fresh);
-                const int ns = __popcll(fm);
-                if (ns == 0) continue;
-                const int32_t myid = compact_lanes(v, fm);
-                const float dd = Q.eval(ix, ns, lane < ns ? myid : 0);
-                merge<LP>(pool, lane < ns ? make_key(dd, myid) : kEmpty, ns, L, W.st_key, W.st_flag);
-                continue;
-            }
-        }
         int nen = 0;
         int64_t scanned = nent;
         for (int64_t off = 0; off < nent && nen < B; off += 64) {
@@ -951,23 +1140,9 @@ __device__ void traverse(const DevIndex& ix, const SearchLaunch& A, int64_t gvis
     }
     }
 
-    // a11: output, rank -> original id, padding
-#pragma unroll
-    for (int s = 0; s < LP; ++s) {
-        const int p = s * 64 + lane;
-        if (p < k) {
-            int32_t oid = -1;
-            float od = __int_as_float(0x7f800000);
-            if (p < pool.np) {
-                oid = ix.perm[(uint32_t)pool.key[s]];
-                od = __uint_as_float((uint32_t)(pool.key[s] >> 32));
-            }
-            A.ids[qi * k + p] = oid;
-            A.dists[qi * k + p] = od;
-        }
-    }
+    write_results<LP>(ix, A, qi, pool.key, pool.np);
     // the traversal's columns; the shared scan's row count is written by the scan
-    if (!LEAN && A.stats && lane < FROG_STAT_SCANROWS) {
+    if (A.stats && lane < FROG_STAT_SCANROWS) {
         int32_t val = 0;
 #pragma unroll
         for (int i = 0; i < FROG_STAT_SCANROWS; ++i)

@@ -55,7 +55,8 @@ void s_search_kernel(SParams P) {
             np += __popcll(ballot(pool.key[s] != kEmpty));
         }
         pool.np = np;
-        traverse<C, LP, XT, LEAN>(ix, A, P.gvis_words, Q, pool, W, vis);
+        if constexpr (LEAN) traverse_lean<C, LP, XT>(ix, A, Q, pool, W, vis);
+        else traverse<C, LP, XT>(ix, A, P.gvis_words, Q, pool, W, vis);
     }
 }
 

@@ -230,3 +230,16 @@ def test_empty_and_single_query_batches(tiny, mode):
     o_ids, o_d, _ = oracle.search(tiny.ox, tiny.Q[3:4], tiny.lo[3:4], tiny.hi[3:4], 10, 64, qidx=np.array([0]),
                                   epn=16, epn_frac=1.0, epn_max=2000, entry_mode=mode)
     assert_parity(ids.cpu().numpy(), ds.cpu().numpy(), o_ids, o_d)
+
+
+@pytest.mark.parametrize("L,budget", [(11, 3), (63, 64), (65, 33), (127, 16), (129, 64), (192, 7), (193, 32), (255, 64)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_lean_traversal_pool_edges(tiny, L, budget, mode):
+    # the timed traversal (no statistics) at pool sizes around its registers'
+    # ends, with budgets that end inside the first 64 candidates and beyond
+    # them, and a table small enough to forget most visited vertices
+    for h in (6, 10):
+        p = dict(epn=16, epn_frac=0.02, epn_max=100, budget=budget, entry_mode=mode)
+        g_ids, g_d = tiny.gpu(10, L, hash_log2=h, **p)
+        o_ids, o_d, _ = tiny.cpu(10, L, **p)
+        assert_parity(g_ids, g_d, o_ids, o_d)
