@@ -48,7 +48,7 @@ void coop_kernel(KParams P) {
     uint64_t* ctl = reinterpret_cast<uint64_t*>(smem + (size_t)kWavesPerBlock * P.lds_per_wave);
     if (threadIdx.x == 0) *ctl = ctl_word(kCtlNone, 0, 0);
     __syncthreads();
-    WaveLds<LP> W(smem, P.lds_per_wave, A.hash_log2);
+    WaveLds<LP> W(smem, P.lds_per_wave, A.hash_log2, ix.dp);
     Visited vis;
     vis.tab = W.tab;
     vis.shift = 32 - A.hash_log2;
@@ -130,7 +130,7 @@ void coop_kernel(KParams P) {
         const int ci = (int)cc, nch = (int)cn;
         QueryCtx<C, XT> Q;
         Q.load(ix, A, P.lr, qi);
-        Q.load_vector(ix);
+        Q.load_vector(ix, W.qbuf);
         Pool<LP> pool;
         const int64_t e0 = (int64_t)ci * P.chunk;
         const int64_t e1 = e0 + P.chunk < Q.ne ? e0 + P.chunk : Q.ne;
@@ -261,7 +261,7 @@ int launch_search_ws(const DevIndex& ix, const SearchLaunch& a, void* stream_v, 
     hipStream_t stream = (hipStream_t)stream_v;
     if (a.entry_mode == 1) return launch_shared(ix, a, stream, wsv, ws_cap);
     const KernelFn fn = pick_kernel(ix.dp, a.L, ix.storage, lean_launch(a));
-    const int lpw = lds_per_wave(a.L, a.hash_log2);
+    const int lpw = lds_per_wave(a.L, a.hash_log2, ix.dp);
     const int smem = lpw * kWavesPerBlock + 16;
     if (smem > 160 * 1024) return fail(FROG_EUNSUPPORTED, "LDS per block %d too large", smem);
     if (smem > 64 * 1024) {
@@ -272,7 +272,18 @@ int launch_search_ws(const DevIndex& ix, const SearchLaunch& a, void* stream_v, 
     const int64_t emax = a.epn_frac > 0.0 ? (a.epn_max > a.epn ? a.epn_max : a.epn) : a.epn;
     int64_t chunk = FROG_CHUNK;
     if ((emax + chunk - 1) / chunk > 16) chunk = ((emax + 15) / 16 + 15) / 16 * 16;
-    const int cpq = (int)((emax + chunk - 1) / chunk);
+    int cpq = (int)((emax + chunk - 1) / chunk);
+    // batches too small for two chunks per resident wavefront: about four
+    // chunks per query, one for each wavefront of its workgroup (1,000
+    // queries of 1,024 entry points, 40k x 960: 1012 us with chunks of 768,
+    // 996 us with 256); larger batches keep the long chunks, whose pools
+    // cost fewer merges
+    const int64_t waves = (int64_t)max_blocks((const void*)fn, smem) * kWavesPerBlock;
+    if (a.hash_log2 > 0 && a.nq * cpq < 2 * waves && cpq < 4) {
+        chunk = ((emax + 3) / 4 + 15) / 16 * 16;
+        chunk = chunk < 64 ? 64 : chunk;
+        cpq = (int)((emax + chunk - 1) / chunk);
+    }
     if (a.nq >= ((int64_t)1 << 31) - 1) return fail(FROG_EINVAL, "nq=%lld too large", (long long)a.nq);
     const int lp = lp_of(a.L);
     int blocks = max_blocks((const void*)fn, smem);

@@ -432,13 +432,13 @@ __device__ __forceinline__ double sum64(double s) {
 // differences and squares in double, summed over the lane's chunks in order
 // and then over the wavefront by sum64.  Rows of up to 1024 padded
 // dimensions (4 chunks per lane) keep the query's chunks in registers for
-// the call and issue a candidate's four loads together (a chunk past the
+// the call (read from qlds, a zero-padded copy in LDS, if there is one) and issue a candidate's four loads together (a chunk past the
 // row reads the row's last chunk, its terms zeroed), two candidates in
 // flight.
 // Wider rows loop over their chunks.  Lane j < cnt receives candidate j's
 // distance; lanes from cnt on receive an unspecified value.
 __device__ float eval_large(const float* __restrict__ X, int dp, const float* __restrict__ q, int d, int cnt,
-                            int32_t myid) {
+                            int32_t myid, const float* qlds = nullptr) {
     const int lane = lane_id();
     const float4* __restrict__ X4 = reinterpret_cast<const float4*>(X);
     const int dp4 = dp >> 2;
@@ -449,6 +449,10 @@ __device__ float eval_large(const float* __restrict__ X, int dp, const float* __
         const float* qq = q;
         asm volatile("" : "+v"(qq));
         float4 qc[4];
+        if (qlds) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qc[i] = reinterpret_cast<const float4*>(qlds)[lane + 64 * i];
+        } else
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int b = 4 * (lane + 64 * i);
@@ -642,20 +646,27 @@ struct Visited {
 
 // ------------------------------------------------------------------ kernel
 
+// Rows of 129 to 1024 floats keep the query in LDS (a 1024-float buffer per
+// wavefront, padded with zeros): the 64-lane distance reads it on every call,
+// and the traversal calls it for about three candidates at a time.
+__host__ __device__ inline int query_lds(int dp) { return dp > 128 && dp <= 1024 ? 4096 : 0; }
+
 // Per-wave LDS: pool staging (64 LP keys + flags), the EN list, the visited
-// table.
+// table, the query of long rows.
 template <int LP>
 struct WaveLds {
     uint64_t* st_key;
     uint32_t* st_flag;
     int32_t* enbuf;
     int32_t* tab;
-    __device__ WaveLds(char* smem, int lds_per_wave, int hash_log2) {
+    float* qbuf;
+    __device__ WaveLds(char* smem, int lds_per_wave, int hash_log2, int dp) {
         char* wbase = smem + (size_t)(threadIdx.x >> 6) * lds_per_wave;
         st_key = reinterpret_cast<uint64_t*>(wbase);
         st_flag = reinterpret_cast<uint32_t*>(st_key + 64 * LP);
         enbuf = reinterpret_cast<int32_t*>(st_flag + 64 * LP);
         tab = hash_log2 > 0 ? enbuf + 64 : nullptr;
+        qbuf = query_lds(dp) ? reinterpret_cast<float*>(enbuf + 64 + (hash_log2 > 0 ? (1 << hash_log2) : 0)) : nullptr;
     }
 };
 
@@ -687,6 +698,7 @@ template <int C, typename XT = float>
 struct QueryCtx {
     float4 qv[C > 0 ? C : 1];
     const float* qrow;
+    const float* qlds = nullptr;   // C = 0: the query in LDS (rows of up to 1024 floats)
     int64_t qi, l, r, cnt, E, ne;
     double rE;
     bool all;
@@ -718,7 +730,15 @@ struct QueryCtx {
         qkey = (uint64_t)(A.qbase + q) << 32;
         qrow = A.Q + q * ix.d;
     }
-    __device__ void load_vector(const DevIndex& ix) {
+    __device__ void load_vector(const DevIndex& ix, float* qbuf) {
+        if constexpr (C == 0) {
+            qlds = qbuf;
+            if (qbuf) {
+                wave_sync();
+                for (int c = lane_id(); c < 1024; c += 64) qbuf[c] = c < ix.d ? qrow[c] : 0.f;
+                wave_sync();
+            }
+        }
         if constexpr (C > 0) {
             const int lane = lane_id();
 #pragma unroll
@@ -748,18 +768,18 @@ struct QueryCtx {
     }
     __device__ float eval(const DevIndex& ix, int nb, int32_t myid) const {
         if constexpr (C > 0) return eval_small<C, XT>(rows_of<XT>(ix), ix.dp, qv, nb, myid);
-        else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, myid);
+        else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, myid, qlds);
     }
     // one step of the lean traversal: C > 0 the group's vector, else lane j's
     // candidate j < nb
     template <bool KEEP>
     __device__ __forceinline__ float eval_groups(const DevIndex& ix, int nb, int32_t id) const {
         if constexpr (C > 0) return eval_group8<C, KEEP, XT>(rows_of<XT>(ix), ix.dp, qv, id);
-        else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, id);
+        else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, id, qlds);
     }
     __device__ float eval_batch(const DevIndex& ix, int nb, int32_t myid) const {
         if constexpr (C > 0) return eval_pipelined<C, XT>(rows_of<XT>(ix), ix.dp, qv, nb, myid);
-        else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, myid);
+        else return eval_large(ix.X, ix.dp, qrow, ix.d, nb, myid, qlds);
     }
 };
 
@@ -1153,9 +1173,9 @@ __device__ void traverse(const DevIndex& ix, const SearchLaunch& A, int64_t gvis
 
 inline int lp_of(int L) { return L <= 64 ? 1 : (L <= 128 ? 2 : 4); }
 
-inline int lds_per_wave(int L, int hash_log2) {
+inline int lds_per_wave(int L, int hash_log2, int dp) {
     const int lp = lp_of(L);
-    return 64 * lp * 8 + 64 * lp * 4 + 64 * 4 + (hash_log2 > 0 ? (4 << hash_log2) : 0);
+    return 64 * lp * 8 + 64 * lp * 4 + 64 * 4 + (hash_log2 > 0 ? (4 << hash_log2) : 0) + query_lds(dp);
 }
 
 // workgroups of kernel `fn` (`threads` threads, `smem` bytes of LDS) the

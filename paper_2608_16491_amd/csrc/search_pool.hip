@@ -53,16 +53,17 @@ __device__ __forceinline__ float pool_eval(const DevIndex& ix, const QC& Q, int 
 }
 
 // The pool of each query: one wavefront per query.  Six wavefronts per
-// SIMD for pools of at most 64, three above (no spill either way).
+// SIMD for pools of at most 64 over rows of at most 128 values, three
+// otherwise (no spill either way).
 template <int C, int LP, int KK, typename XT = float, int MK = (KK > 64 ? KK : 64)>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LP == 1 ? 6 : 3))) void s_pool_kernel(SParams P) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LP == 1 && C > 0 ? 6 : 3))) void s_pool_kernel(SParams P) {
     using namespace topk;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const DevIndex& ix = P.ix;
     const SearchLaunch& A = P.a;
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
-    WaveLds<LP> W(smem, P.lds_per_wave, 0);
+    WaveLds<LP> W(smem, P.lds_per_wave, 0, ix.dp);
     char* lbase = smem + (size_t)wave * P.lds_per_wave + P.lds_list;
     // KK: entries of each chunk list the scan left (their stride); the merged
     // list keeps MK >= 64 of them (an offer of 64 fits after a cut), twice
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(LP == 1 
         const SPlan* pp = P.plan + qi;
         QueryCtx<C, XT> Q;
         Q.qrow = A.Q + qi * ix.d;
-        Q.load_vector(ix);   // issued beside the plan's load
+        Q.load_vector(ix, W.qbuf);   // issued beside the plan's load
         const SPlan p = *pp;
         if (p.l > p.r) return;
         Q.set(ix, A, qi, p.l, p.r);

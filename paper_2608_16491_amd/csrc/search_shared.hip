@@ -318,10 +318,10 @@ int launch_shared(const DevIndex& ix, const SearchLaunch& a, hipStream_t stream,
     auto sfn = pick_s_search(ix.dp, a.L, ix.storage, lean_launch(a));
     auto pfn = pick_s_pool(ix.dp, a.L, ix.storage);
     // search kernel: pool staging, EN list and visited table per wave
-    const int lps = lds_per_wave(a.L, a.hash_log2);
+    const int lps = lds_per_wave(a.L, a.hash_log2, ix.dp);
     const int smem = lps * kWavesPerBlock;
     // pool kernel: pool staging and EN list, then the re-rank list
-    const int base_lds = lds_per_wave(a.L, 0);
+    const int base_lds = lds_per_wave(a.L, 0, ix.dp);
     const int lpw = base_lds + 2 * pool_kkeep(kkeep, a.L) * 8 + 16;
     const int smem_pool = lpw;   // one wavefront (query) per workgroup, as for the scan
     if (smem > 160 * 1024 || smem_pool > 160 * 1024)

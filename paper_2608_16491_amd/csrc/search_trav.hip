@@ -11,14 +11,14 @@ namespace {
 // covers (no candidate is new, the traversal is short) and the empty ones,
 // which then fill the kernel's tail (the results do not depend on the order).
 template <int C, int LP, typename XT = float, bool LEAN = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FROG_SEARCH_WAVES_PER_EU)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(C > 0 ? FROG_SEARCH_WAVES_PER_EU : FROG_WAVES_PER_EU)))
 void s_search_kernel(SParams P) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const DevIndex& ix = P.ix;
     const SearchLaunch& A = P.a;
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
-    WaveLds<LP> W(smem, P.lds_search, A.hash_log2);
+    WaveLds<LP> W(smem, P.lds_search, A.hash_log2, ix.dp);
     Visited vis;
     vis.tab = W.tab;
     vis.shift = 32 - A.hash_log2;
@@ -41,7 +41,7 @@ void s_search_kernel(SParams P) {
         }
         QueryCtx<C, XT> Q;
         Q.set(ix, A, qi, p.l, p.r);   // the plan's rank interval
-        Q.load_vector(ix);
+        Q.load_vector(ix, W.qbuf);
         Q.shared = true;
         Q.T = p.T;
         Q.pkey = A.lv.key;
