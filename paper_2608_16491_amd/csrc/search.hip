@@ -179,7 +179,10 @@ void coop_kernel(KParams P) {
     }
 }
 
-__global__ void rank_bounds_kernel(DevIndex ix, const double* lo, const double* hi, int64_t nq, int32_t* lr) {
+// One wavefront per query; with counter (the search's prologue), the work
+// counter and the query's finished-chunk count are cleared as well.
+__global__ void rank_bounds_kernel(DevIndex ix, const double* lo, const double* hi, int64_t nq, int32_t* lr,
+                                   unsigned int* counter, unsigned int* done) {
     const int64_t q = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     if (q >= nq) return;
     int64_t l, r;
@@ -187,13 +190,11 @@ __global__ void rank_bounds_kernel(DevIndex ix, const double* lo, const double* 
     if (lane_id() == 0) {
         lr[2 * q] = (int32_t)l;
         lr[2 * q + 1] = (int32_t)r;
+        if (counter) {
+            done[q] = 0u;
+            if (q == 0) *counter = 0u;
+        }
     }
-}
-
-__global__ void init_kernel(unsigned int* counter, unsigned int* done, int64_t nq) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) *counter = 0u;
-    if (i < nq) done[i] = 0u;
 }
 
 using KernelFn = void (*)(KParams);
@@ -331,9 +332,9 @@ int launch_search_ws(const DevIndex& ix, const SearchLaunch& a, void* stream_v, 
     P.done = reinterpret_cast<unsigned int*>(base + off_done);
     P.part = reinterpret_cast<uint64_t*>(base + off_part);
     P.gvis = reinterpret_cast<uint32_t*>(base + off_gvis);
-    hipLaunchKernelGGL(init_kernel, dim3((unsigned)((a.nq + 255) / 256)), dim3(256), 0, stream, P.counter, P.done, a.nq);
     const int64_t rb_blocks = (a.nq + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(rank_bounds_kernel, dim3((unsigned)rb_blocks), dim3(kBlock), 0, stream, ix, a.lo, a.hi, a.nq, lr);
+    hipLaunchKernelGGL(rank_bounds_kernel, dim3((unsigned)rb_blocks), dim3(kBlock), 0, stream, ix, a.lo, a.hi, a.nq, lr,
+                       P.counter, P.done);
     hipEvent_t* ev = reinterpret_cast<hipEvent_t*>(a.events);
     if (ev) (void)hipEventRecord(ev[0], stream);
     hipLaunchKernelGGL(fn, dim3(blocks), dim3(kBlock), smem, stream, P);
@@ -371,7 +372,8 @@ int launch_rank_bounds(const DevIndex& ix, const double* lo, const double* hi, i
                        void* stream_v) {
     hipStream_t stream = (hipStream_t)stream_v;
     const int64_t blocks = (nq + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(rank_bounds_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, ix, lo, hi, nq, lr);
+    hipLaunchKernelGGL(rank_bounds_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, ix, lo, hi, nq, lr,
+                       (unsigned int*)nullptr, (unsigned int*)nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(FROG_EHIP, "rank_bounds launch: %s", hipGetErrorString(e));
     return FROG_OK;

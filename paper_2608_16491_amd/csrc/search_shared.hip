@@ -51,6 +51,8 @@ __device__ int64_t half_count(const TA* __restrict__ a, int64_t n, F below) {
 // searched side by side, one per half-wave), the threshold, the level, the
 // run of the level's list (again one bound per half-wave), its windows, and
 // a bucket and place per window (lane wi takes window wi).
+// SMALL: no buckets and no places (s_small_kernel orders the pairs).
+template <bool SMALL>
 __global__ __launch_bounds__(kBlock) void s_plan_kernel(SParams P) {
     const int64_t q = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     if (q >= P.a.nq) return;   // wave-uniform
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(kBlock) void s_plan_kernel(SParams P) {
     }
     // a place in the bucket of each window (none when the run meets more
     // than kSMaxWin windows: the pool kernel then evaluates the sample exactly)
-    if (p.nw <= kSMaxWin && lane < p.nw) {
+    if (!SMALL && p.nw <= kSMaxWin && lane < p.nw) {
         const int bin = pair_bin(P, q, p.lev, p.a, p.b, p.w0, lane);
         P.plan[q].pos[lane] = (int32_t)atomicAdd(P.hist + bin, 1u);
     }
@@ -116,7 +118,7 @@ __global__ __launch_bounds__(kBlock) void s_plan_kernel(SParams P) {
         // the range: long traversals) before class 1 (covered or empty
         // ranges: short ones), each class spread over kQSub counters
         const int cls = p.l > p.r || p.all ? 1 : 0;
-        dst->qpos = (int32_t)atomicAdd(P.qhist + (cls * kQSub + (q & (kQSub - 1))) * kQLine, 1u);
+        if (!SMALL) dst->qpos = (int32_t)atomicAdd(P.qhist + (cls * kQSub + (q & (kQSub - 1))) * kQLine, 1u);
         dst->l = p.l;
         dst->r = p.r;
         dst->T = p.T;
@@ -241,17 +243,11 @@ __global__ void s_order_kernel(SParams P) {
             (int32_t)(q * kSMaxWin + wi);
 }
 
-// one wavefront per tile: lanes 0..15 take its slots, each slot the piece of
-// its query's run inside the tile's window
-__global__ __launch_bounds__(kBlock) void s_tile_kernel(SParams P) {
+// One wavefront builds tile t: lanes 0..15 take its slots (e: pair id or -1),
+// each slot the piece of its query's run inside the tile's window.
+__device__ __forceinline__ void build_tile(const SParams& P, int64_t t, int32_t e, int64_t ntiles) {
     const int lane = lane_id();
-    const int64_t t = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (t >= P.tmax) return;
-    const int64_t places = P.meta[0];
     STile* T = P.tiles + t;
-    const int64_t i = t * kSQ + lane;
-    int32_t e = -1;
-    if (lane < kSQ && i < places) e = P.order[i];
     const int32_t q = e >= 0 ? e / kSMaxWin : -1;
     const int wi = e >= 0 ? e % kSMaxWin : 0;
     SPlan* p = P.plan + (q >= 0 ? q : 0);
@@ -293,7 +289,6 @@ __global__ __launch_bounds__(kBlock) void s_tile_kernel(SParams P) {
     // to 4 times as many chunks, so that the round that ends the scan is
     // short (with fewer tiles than slots, as many tiles are cut as still fit
     // in one round)
-    const int64_t ntiles = P.meta[1];
     const int64_t nfit = (P.scan_slots - ntiles) / 3;   // a tile cut in 4 adds 3 items
     const int64_t nsplit = ntiles > P.scan_slots ? ntiles - P.scan_slots : (nfit < ntiles ? nfit : ntiles);
     const int64_t span = (int64_t)ub - ua;
@@ -307,6 +302,109 @@ __global__ __launch_bounds__(kBlock) void s_tile_kernel(SParams P) {
         T->ua = nq > 0 ? ua : 0;
         T->ub = nq > 0 ? ub : 0;
         T->nq = nq;
+    }
+}
+
+// one wavefront per tile
+__global__ __launch_bounds__(kBlock) void s_tile_kernel(SParams P) {
+    const int lane = lane_id();
+    const int64_t t = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    if (t >= P.tmax) return;
+    const int64_t places = P.meta[0];
+    const int64_t i = t * kSQ + lane;
+    build_tile(P, t, lane < kSQ && i < places ? P.order[i] : -1, P.meta[1]);
+}
+
+// Batches of at most kSmallQ queries: one workgroup orders the pairs by bucket
+// (a bitonic sort of at most 1024 keys in LDS in place of counters, offsets
+// and scattered places), cuts each window's pairs into tiles of 16, builds the
+// tiles and sets the query order.  With the plan kernel before it this
+// replaces five of the six planning launches, each of which takes about 4.5
+// us however small the batch (12 queries: 139 -> 130 us per call; at 100
+// queries the sort takes what the launches did).
+__global__ __launch_bounds__(1024) void s_small_kernel(SParams P) {
+    __shared__ uint64_t key[kSmallQ * kSMaxWin];
+    __shared__ int32_t head[kSmallQ * kSMaxWin];   // first sorted pair of each tile
+    __shared__ int wsum[16], wmax[16], w0sum[2];
+    static_assert(kSmallQ * kSMaxWin == 1024, "one thread per pair");
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int nq = (int)P.a.nq;
+    // pair t: window t % kSMaxWin of query t / kSMaxWin
+    const int q = t / kSMaxWin, wi = t % kSMaxWin;
+    uint64_t k = ~0ull;
+    if (q < nq) {
+        const SPlan* p = P.plan + q;
+        if (p->l <= p->r && p->nw <= kSMaxWin && wi < p->nw)
+            k = ((uint64_t)pair_bin(P, q, p->lev, p->a, p->b, p->w0, wi) << 32) | (uint32_t)t;
+    }
+    // thread t < nq: whether query t comes late in the traversal's order
+    static_assert(kSmallQ <= 128, "the batch's queries in the first two wavefronts");
+    const bool late = t < nq && (P.plan[t].l > P.plan[t].r || P.plan[t].all);
+    const uint64_t om = ballot(t < nq && !late);   // the early ones
+    if (lane == 0 && wave < 2) w0sum[wave] = __popcll(om);
+    int n2 = 64;   // keys sorted: a power of two that holds the batch's pairs
+    while (n2 < nq * kSMaxWin) n2 <<= 1;
+    // exchanges within a wavefront go through lane shuffles, wider ones
+    // through LDS
+    for (int kb = 2; kb <= n2; kb <<= 1)
+        for (int jb = kb >> 1; jb > 0; jb >>= 1) {
+            uint64_t other;
+            if (jb < 64) {
+                other = (uint64_t)__shfl_xor((long long)k, jb);
+            } else {
+                key[t] = k;
+                __syncthreads();
+                other = key[t ^ jb];
+                __syncthreads();
+            }
+            const bool low = (t & jb) == 0, up = (t & kb) == 0;
+            k = (low == up) ? (other < k ? other : k) : (other > k ? other : k);
+        }
+    key[t] = t < n2 ? k : ~0ull;
+    __syncthreads();
+    // the first pair of t's window (a maximum over the window starts up to
+    // t), whether t starts a tile, and how many tiles start before it
+    const bool valid = t < n2 && key[t] != ~0ull;
+    auto win = [&](int i) { return (int)(key[i] >> 32) / kSPer; };
+    int first = valid && (t == 0 || win(t) != win(t - 1)) ? t : -1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(first, o);
+        if (lane >= o) first = first > v ? first : v;
+    }
+    if (lane == 63) wmax[wave] = first;
+    __syncthreads();
+    for (int i = 0; i < wave; ++i) first = first > wmax[i] ? first : wmax[i];
+    const bool starts = valid && (t - first) % kSQ == 0;
+    const uint64_t sm = ballot(starts);
+    if (lane == 0) wsum[wave] = __popcll(sm);
+    __syncthreads();
+    int at = mbcnt(sm), ntiles = 0;
+    for (int i = 0; i < 16; ++i) {
+        at += i < wave ? wsum[i] : 0;
+        ntiles += wsum[i];
+    }
+    if (starts) head[at] = t;
+    // the traversal's order: queries whose sample is a strict subset of their
+    // range, then the others
+    if (t < nq) {
+        const int n0 = w0sum[0] + w0sum[1], before = wave == 1 ? w0sum[0] : 0;
+        P.qorder[late ? n0 + wave * 64 - before + mbcnt(~om) : before + mbcnt(om)] = t;
+    }
+    if (t == 0) {
+        P.meta[0] = (uint32_t)ntiles * kSQ;
+        P.meta[1] = (uint32_t)ntiles;
+        P.meta[2] = 0u;
+    }
+    __syncthreads();
+    for (int64_t i = ntiles + t; i < P.tmax; i += 1024) P.tiles[i].nq = 0;   // unused
+    for (int i = wave; i < ntiles; i += 16) {
+        int32_t e = -1;
+        if (lane < kSQ) {
+            const int j = head[i] + lane;
+            if (j < n2 && key[j] != ~0ull && win(j) == win(head[i])) e = (int32_t)(uint32_t)key[j];
+        }
+        build_tile(P, i, e, ntiles);
     }
 }
 
@@ -395,6 +493,9 @@ int launch_shared(const DevIndex& ix, const SearchLaunch& a, hipStream_t stream,
     // places: at most kSMaxWin pairs per query, plus up to 15 of padding per window
     const int64_t norder = (int64_t)kSMaxWin * a.nq + (int64_t)kSQ * P.nwin;
     P.tmax = (norder + kSQ - 1) / kSQ;
+    // small batches: a tile per pair at most
+    const bool small = a.nq <= kSmallQ;
+    if (small && P.tmax > kSMaxWin * a.nq) P.tmax = kSMaxWin * a.nq;
     P.scan_slots = scan_slots;
     P.nbins = P.nwin * kSPer;
     P.kkeep = kkeep;
@@ -470,16 +571,21 @@ int launch_shared(const DevIndex& ix, const SearchLaunch& a, hipStream_t stream,
     // events: before the matrix-core scan, after it, after the search kernel
     // (the planning kernels come before the first, the pool kernel after the
     // second)
-    const int64_t ninit = norder > P.nbins ? norder : P.nbins;
-    hipLaunchKernelGGL(s_init_kernel, dim3((unsigned)((ninit + 255) / 256)), dim3(256), 0, stream, P.meta, P.qhist,
-                       P.hist, P.nbins, P.order, norder);
     const int64_t plan_blocks = (a.nq + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(s_plan_kernel, dim3((unsigned)plan_blocks), dim3(kBlock), 0, stream, P);
-    hipLaunchKernelGGL(s_wprefix_kernel, dim3((unsigned)((P.nwin + 255) / 256)), dim3(256), 0, stream, P);
-    hipLaunchKernelGGL(s_wscan_kernel, dim3(1), dim3(1024), 0, stream, P);
-    hipLaunchKernelGGL(s_order_kernel, dim3(qb), dim3(256), 0, stream, P);
-    hipLaunchKernelGGL(s_tile_kernel, dim3((unsigned)((P.tmax + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock),
-                       0, stream, P);
+    if (small) {
+        hipLaunchKernelGGL(s_plan_kernel<true>, dim3((unsigned)plan_blocks), dim3(kBlock), 0, stream, P);
+        hipLaunchKernelGGL(s_small_kernel, dim3(1), dim3(1024), 0, stream, P);
+    } else {
+        const int64_t ninit = norder > P.nbins ? norder : P.nbins;
+        hipLaunchKernelGGL(s_init_kernel, dim3((unsigned)((ninit + 255) / 256)), dim3(256), 0, stream, P.meta, P.qhist,
+                           P.hist, P.nbins, P.order, norder);
+        hipLaunchKernelGGL(s_plan_kernel<false>, dim3((unsigned)plan_blocks), dim3(kBlock), 0, stream, P);
+        hipLaunchKernelGGL(s_wprefix_kernel, dim3((unsigned)((P.nwin + 255) / 256)), dim3(256), 0, stream, P);
+        hipLaunchKernelGGL(s_wscan_kernel, dim3(1), dim3(1024), 0, stream, P);
+        hipLaunchKernelGGL(s_order_kernel, dim3(qb), dim3(256), 0, stream, P);
+        hipLaunchKernelGGL(s_tile_kernel, dim3((unsigned)((P.tmax + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock),
+                           0, stream, P);
+    }
     if (ev) (void)hipEventRecord(ev[0], stream);
     hipLaunchKernelGGL(scan, dim3((unsigned)((items + scan_waves - 1) / scan_waves)), dim3(64 * scan_waves), smem_scan,
                        stream, P);

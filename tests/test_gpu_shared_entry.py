@@ -269,3 +269,22 @@ def test_shared_query_order_classes(tiny, kind):
     assert_parity(g_ids, g_d, o_ids, o_d, max_residual=0 if kind == "all_empty" else 1)
     if kind == "all_empty":
         assert (g_ids == -1).all()
+
+
+@pytest.mark.parametrize("nq", [1, 2, 8, 9, 63, 64, 65, 127, 128, 129])
+def test_shared_small_batches(nq):
+    # batches up to 128 queries are planned by the one-workgroup kernel: sizes
+    # around its wavefronts and powers of two of pairs, with empty, covered
+    # and wide ranges among them, and runs over up to 8 windows and more
+    print(f"[gpu] shared entry sample: small batch nq={nq}", flush=True)
+    w = workloads.make("tiny", n=12000, nq=nq)
+    lo, hi = w.lo.copy(), w.hi.copy()
+    lo[::5], hi[::5] = 7, 3                 # empty
+    lo[1::5], hi[1::5] = 100, 400           # covered by the sample
+    lo[2::5], hi[2::5] = 0, 11999
+    c = Case(w.X, w.attr, w.Q, lo, hi)
+    for emax in (600, 9000):
+        p = dict(SH, epn_max=emax)
+        g_ids, g_d = c.gpu(10, 32, **p)
+        o_ids, o_d, _ = c.cpu(10, 32, **p)
+        assert_parity(g_ids, g_d, o_ids, o_d)
