@@ -274,13 +274,13 @@ int launch_search_ws(const DevIndex& ix, const SearchLaunch& a, void* stream_v, 
     int64_t chunk = FROG_CHUNK;
     if ((emax + chunk - 1) / chunk > 16) chunk = ((emax + 15) / 16 + 15) / 16 * 16;
     int cpq = (int)((emax + chunk - 1) / chunk);
-    // batches too small for two chunks per resident wavefront: about four
-    // chunks per query, one for each wavefront of its workgroup (1,000
-    // queries of 1,024 entry points, 40k x 960: 1012 us with chunks of 768,
-    // 996 us with 256); larger batches keep the long chunks, whose pools
-    // cost fewer merges
+    // few queries (a workgroup each, and then some to spare): about four
+    // chunks per query, one for each wavefront of its workgroup.  Larger
+    // batches keep the long chunks, whose pools cost fewer merges (1,004
+    // queries of 970 entry points, 14k x 20: 186 us with chunks of 768, 191
+    // us with 256)
     const int64_t waves = (int64_t)max_blocks((const void*)fn, smem) * kWavesPerBlock;
-    if (a.hash_log2 > 0 && a.nq * cpq < 2 * waves && cpq < 4) {
+    if (a.hash_log2 > 0 && a.nq * cpq <= waves / 4 && cpq < 4) {
         chunk = ((emax + 3) / 4 + 15) / 16 * 16;
         chunk = chunk < 64 ? 64 : chunk;
         cpq = (int)((emax + chunk - 1) / chunk);

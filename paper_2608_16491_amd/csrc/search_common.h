@@ -354,6 +354,31 @@ __device__ __forceinline__ float eval_group8(const XT* __restrict__ X, int dp, c
     return (float)sum8(s);
 }
 
+// Two such steps, their loads in flight together.
+template <int C, typename XT = float>
+__device__ __forceinline__ void eval_group8x2(const XT* __restrict__ X, int dp, const float4 (&qv)[C], int32_t id0, int32_t id1,
+                                              float& d0, float& d1) {
+    float4 x[2][C];
+    const int sub = lane_id() & 7;
+    load_row<C, XT>(X, dp, id0, sub, true, x[0]);
+    load_row<C, XT>(X, dp, id1, sub, true, x[1]);
+    double s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const double q0 = qv[c].x, q1 = qv[c].y, q2 = qv[c].z, q3 = qv[c].w;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            double t;
+            t = q0 - (double)x[g][c].x; s[g] = __builtin_fma(t, t, s[g]);
+            t = q1 - (double)x[g][c].y; s[g] = __builtin_fma(t, t, s[g]);
+            t = q2 - (double)x[g][c].z; s[g] = __builtin_fma(t, t, s[g]);
+            t = q3 - (double)x[g][c].w; s[g] = __builtin_fma(t, t, s[g]);
+        }
+    }
+    d0 = (float)sum8(s[0]);
+    d1 = (float)sum8(s[1]);
+}
+
 // Same result as eval_small for the entry-point batches (1..64 candidates),
 // with two steps of 16 vectors in flight: the loads of step i+1 are issued
 // before step i is reduced, so the arithmetic overlaps the memory latency.
@@ -968,17 +993,32 @@ __device__ void traverse_lean(const DevIndex& ix, const SearchLaunch& A, const Q
                     if (fresh) W.enbuf[mbcnt(fm)] = v;
                     wave_sync();
                     constexpr int G = C > 0 ? 8 : 64;   // candidates per step
-                    for (int j0 = 0; j0 < ns; j0 += G) {
-                        const int j = C > 0 ? j0 + (lane >> 3) : lane;
-                        const int32_t id = W.enbuf[j < ns ? j : ns - 1];
-                        // a8
-                        const float dd = Q.template eval_groups<(LP > 1)>(ix, ns, id);
-                        // a9 + a10: MergeTopEfS
-                        const uint64_t nkey = make_key(dd, id);
+                    // a9 + a10 (MergeTopEfS) of a step's keys: lane group j0 + g
+                    // (C = 0: lane g) holds candidate g
+                    auto absorb = [&](uint64_t nkey, int j) {
                         bool cand = j < ns && (C == 0 || (lane & 7) == 0);
                         if (pool.np >= L) cand = cand && nkey < key_at<LP>(pool.key, L - 1);
                         for (uint64_t mm = ballot(cand); mm; mm &= mm - 1)
                             insert_key<LP>(pool.key, open, pool.np, L, readlane64(nkey, __builtin_ctzll(mm)));
+                    };
+                    for (int j0 = 0; j0 < ns; j0 += G) {
+                        const int j = C > 0 ? j0 + (lane >> 3) : lane;
+                        const int32_t id = W.enbuf[j < ns ? j : ns - 1];
+                        // a8; short rows two steps at a time (unclustered data
+                        // leaves 20 and more fresh candidates of a budget of 32)
+                        if constexpr (C > 0 && C <= 2) {
+                            if (ns - j0 > 8) {
+                                const int32_t id1 = W.enbuf[j + 8 < ns ? j + 8 : ns - 1];
+                                float d0, d1;
+                                eval_group8x2<C, XT>(rows_of<XT>(ix), ix.dp, Q.qv, id, id1, d0, d1);
+                                absorb(make_key(d0, id), j);
+                                absorb(make_key(d1, id1), j + 8);
+                                j0 += 8;
+                                continue;
+                            }
+                        }
+                        const float dd = Q.template eval_groups<(LP > 1)>(ix, ns, id);
+                        absorb(make_key(dd, id), j);
                     }
 #pragma unroll
                     for (int s = 0; s < LP; ++s) open[s] &= slot_mask(L, s);
