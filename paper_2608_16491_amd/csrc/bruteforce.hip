@@ -336,6 +336,8 @@ void bf_scan_kernel(BFParams P, int pass, bool but16) {
     const int sh = 4 * pass;
     __shared__ uint64_t s_key[kBBuf];
     __shared__ uint8_t s_slot[kBBuf];
+    __shared__ uint16_t s_off[kBBuf];
+    __shared__ int32_t s_cnt[kBQ];
     __shared__ int32_t s_q[kBQ], s_l[kBQ], s_r[kBQ];
     __shared__ float s_qn[kBQ];
     constexpr int NB = KT > 0 ? 1 : 4;   // blocks at a time
@@ -348,13 +350,22 @@ void bf_scan_kernel(BFParams P, int pass, bool but16) {
     const int64_t chunk = P.meta->chunk[pass];
     const float inf = __int_as_float(0x7f800000);
     int fill = 0;
-    // the buffered candidates to their queries' lists
+    // the buffered candidates to their queries' lists: each one's place among
+    // its slot's in LDS, one global counter step per slot, then the stores
+    // (a counter step per candidate made each block of a sampling pass, where
+    // every row is a candidate, wait for eight of them in turn)
     auto flush = [&]() {
+        if (fill == 0) return;
+        if (lane < kBQ) s_cnt[lane] = 0;
+        wave_sync();
+        for (int i = lane; i < fill; i += 64) s_off[i] = (uint16_t)atomicAdd(&s_cnt[s_slot[i]], 1);
+        wave_sync();
+        if (lane < kBQ && s_cnt[lane] > 0) s_cnt[lane] = atomicAdd(P.cnt + s_q[lane], s_cnt[lane]);
         wave_sync();
         for (int i = lane; i < fill; i += 64) {
-            const int32_t q = s_q[s_slot[i]];
-            const int32_t at = atomicAdd(P.cnt + q, 1);
-            if (at < P.cap) P.list[(int64_t)q * P.cap + at] = s_key[i];
+            const int sl = s_slot[i];
+            const int32_t at = s_cnt[sl] + s_off[i];
+            if (at < P.cap) P.list[(int64_t)s_q[sl] * P.cap + at] = s_key[i];
         }
         fill = 0;
         wave_sync();
