@@ -1004,13 +1004,20 @@ __device__ void traverse_lean(const DevIndex& ix, const SearchLaunch& A, const Q
                     for (int j0 = 0; j0 < ns; j0 += G) {
                         const int j = C > 0 ? j0 + (lane >> 3) : lane;
                         const int32_t id = W.enbuf[j < ns ? j : ns - 1];
-                        // a8; short rows two steps at a time (unclustered data
-                        // leaves 20 and more fresh candidates of a budget of 32)
-                        if constexpr (C > 0 && C <= 2) {
+                        // a8; two steps before their keys are inserted when
+                        // more than 8 candidates are fresh (unclustered data
+                        // leaves most of the budget), short rows with both
+                        // steps' loads in flight
+                        if constexpr (C > 0) {
                             if (ns - j0 > 8) {
                                 const int32_t id1 = W.enbuf[j + 8 < ns ? j + 8 : ns - 1];
                                 float d0, d1;
-                                eval_group8x2<C, XT>(rows_of<XT>(ix), ix.dp, Q.qv, id, id1, d0, d1);
+                                if constexpr (C <= 2) {
+                                    eval_group8x2<C, XT>(rows_of<XT>(ix), ix.dp, Q.qv, id, id1, d0, d1);
+                                } else {
+                                    d0 = Q.template eval_groups<true>(ix, ns, id);
+                                    d1 = Q.template eval_groups<true>(ix, ns, id1);
+                                }
                                 absorb(make_key(d0, id), j);
                                 absorb(make_key(d1, id1), j + 8);
                                 j0 += 8;
