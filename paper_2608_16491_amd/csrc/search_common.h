@@ -261,30 +261,33 @@ __device__ __forceinline__ float4 widen4(uint32_t w0, uint32_t w1) {
     }
 }
 
-// All C chunks of row `id` for lane `sub` (zeros when !v).  fp16 rows take
-// one 16-byte load per pair of chunks, so that the 8 lanes of a row read
-// 128 contiguous bytes per instruction, as for fp32 rows.
+// One lane's pieces of a row as stored (C = dp / 32 chunks), widened chunk by
+// chunk where they are used.  16-bit rows take one 16-byte load per pair of
+// chunks, so that the 8 lanes of a row read 128 contiguous bytes per
+// instruction, as for fp32 rows.  Their pieces stay as loaded and nothing
+// that uses them is scheduled before the last load: widened beside the load,
+// the compiler waited for each piece before it loaded the next, a memory
+// round trip per piece (150k x 100 bf16, 16 entry points, 777 queries: 264 us
+// per call, 238 so).
 template <int C, typename XT>
-__device__ __forceinline__ void load_row(const XT* __restrict__ X, int dp, int64_t id, int sub, bool v,
-                                         float4 (&x)[C]) {
-    if constexpr (sizeof(XT) == 4) {
+struct Row {
+    static constexpr bool kWide = sizeof(XT) == 4;
+    static_assert(kWide || C % 2 == 0, "16-bit rows come in pairs of chunks");
+    using Piece = std::conditional_t<kWide, float4, uint4>;
+    Piece h[kWide ? C : C / 2];
+    __device__ __forceinline__ void load(const XT* __restrict__ X, int dp, int64_t id, int sub) {
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-            x[c] = v ? reinterpret_cast<const float4*>(X)[id * (dp >> 2) + sub + 8 * c]
-                     : make_float4(0.f, 0.f, 0.f, 0.f);
-    } else {
-        static_assert(C % 2 == 0, "fp16 rows come in pairs of chunks");
-#pragma unroll
-        for (int p = 0; p < C / 2; ++p) {
-            const uint4 h = v ? reinterpret_cast<const uint4*>(X)[id * (dp >> 3) + sub + 8 * p]
-                              : make_uint4(0u, 0u, 0u, 0u);
-            x[2 * p] = widen4<XT>(h.x, h.y);
-            x[2 * p + 1] = widen4<XT>(h.z, h.w);
-        }
+        for (int p = 0; p < (kWide ? C : C / 2); ++p)
+            h[p] = reinterpret_cast<const Piece*>(X)[id * (dp >> (kWide ? 2 : 3)) + sub + 8 * p];
+        if constexpr (!kWide) __builtin_amdgcn_sched_barrier(0);
     }
-}
+    __device__ __forceinline__ float4 chunk(int c) const {
+        if constexpr (kWide) return h[c];
+        else return c & 1 ? widen4<XT>(h[c >> 1].z, h[c >> 1].w) : widen4<XT>(h[c >> 1].x, h[c >> 1].y);
+    }
+};
 
-// The query dimensions a lane pairs with chunk c (the layout of load_row).
+// The query dimensions a lane pairs with chunk c (the layout of Row).
 template <typename XT>
 __device__ __forceinline__ int chunk_dim(int sub, int c) {
     if constexpr (sizeof(XT) == 4) return 4 * (sub + 8 * c);
@@ -308,8 +311,8 @@ __device__ float eval_small(const XT* __restrict__ X, int dp, const float4 (&qv)
     for (int sb0 = 0; sb0 < cnt; sb0 += 8) {
         const int j = sb0 + (lane >> 3);
         const int id = __shfl(myid, (j < cnt ? j : cnt - 1) & 63);
-        float4 x[C];
-        load_row<C, XT>(X, dp, id, sub, true, x);
+        Row<C, XT> row;
+        row.load(X, dp, id, sub);
         double s = 0.0;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
@@ -317,11 +320,12 @@ __device__ float eval_small(const XT* __restrict__ X, int dp, const float4 (&qv)
             float4 qf = qv[c];
             asm volatile("" : "+v"(qf.x), "+v"(qf.y), "+v"(qf.z), "+v"(qf.w));
             const double q0 = qf.x, q1 = qf.y, q2 = qf.z, q3 = qf.w;
+            const float4 x = row.chunk(c);
             double t;
-            t = q0 - (double)x[c].x; s = __builtin_fma(t, t, s);
-            t = q1 - (double)x[c].y; s = __builtin_fma(t, t, s);
-            t = q2 - (double)x[c].z; s = __builtin_fma(t, t, s);
-            t = q3 - (double)x[c].w; s = __builtin_fma(t, t, s);
+            t = q0 - (double)x.x; s = __builtin_fma(t, t, s);
+            t = q1 - (double)x.y; s = __builtin_fma(t, t, s);
+            t = q2 - (double)x.z; s = __builtin_fma(t, t, s);
+            t = q3 - (double)x.w; s = __builtin_fma(t, t, s);
         }
         s = sum8(s);
         // vector sb0 + g sits in lanes 8g..8g+7; lane sb0 + g takes it
@@ -337,42 +341,47 @@ __device__ float eval_small(const XT* __restrict__ X, int dp, const float4 (&qv)
 // the compiler may hold it widened across the caller's loop.
 template <int C, bool KEEP, typename XT = float>
 __device__ __forceinline__ float eval_group8(const XT* __restrict__ X, int dp, const float4 (&qv)[C], int32_t id) {
-    float4 x[C];
-    load_row<C, XT>(X, dp, id, lane_id() & 7, true, x);
+    Row<C, XT> row;
+    row.load(X, dp, id, lane_id() & 7);
     double s = 0.0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         float4 qf = qv[c];
         if constexpr (KEEP) asm volatile("" : "+v"(qf.x), "+v"(qf.y), "+v"(qf.z), "+v"(qf.w));
         const double q0 = qf.x, q1 = qf.y, q2 = qf.z, q3 = qf.w;
+        const float4 x = row.chunk(c);
         double t;
-        t = q0 - (double)x[c].x; s = __builtin_fma(t, t, s);
-        t = q1 - (double)x[c].y; s = __builtin_fma(t, t, s);
-        t = q2 - (double)x[c].z; s = __builtin_fma(t, t, s);
-        t = q3 - (double)x[c].w; s = __builtin_fma(t, t, s);
+        t = q0 - (double)x.x; s = __builtin_fma(t, t, s);
+        t = q1 - (double)x.y; s = __builtin_fma(t, t, s);
+        t = q2 - (double)x.z; s = __builtin_fma(t, t, s);
+        t = q3 - (double)x.w; s = __builtin_fma(t, t, s);
     }
     return (float)sum8(s);
 }
 
-// Two such steps, their loads in flight together.
-template <int C, typename XT = float>
+// Two such steps, their loads in flight together (16-bit rows of 65 to 128
+// values, the call above: 238 us with one step after the other, 217 so).
+template <int C, bool KEEP, typename XT = float>
 __device__ __forceinline__ void eval_group8x2(const XT* __restrict__ X, int dp, const float4 (&qv)[C], int32_t id0, int32_t id1,
                                               float& d0, float& d1) {
-    float4 x[2][C];
+    Row<C, XT> row[2];
     const int sub = lane_id() & 7;
-    load_row<C, XT>(X, dp, id0, sub, true, x[0]);
-    load_row<C, XT>(X, dp, id1, sub, true, x[1]);
+    row[0].load(X, dp, id0, sub);
+    row[1].load(X, dp, id1, sub);
     double s[2] = {0.0, 0.0};
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        const double q0 = qv[c].x, q1 = qv[c].y, q2 = qv[c].z, q3 = qv[c].w;
+        float4 qf = qv[c];
+        if constexpr (KEEP) asm volatile("" : "+v"(qf.x), "+v"(qf.y), "+v"(qf.z), "+v"(qf.w));
+        const double q0 = qf.x, q1 = qf.y, q2 = qf.z, q3 = qf.w;
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
+            const float4 x = row[g].chunk(c);
             double t;
-            t = q0 - (double)x[g][c].x; s[g] = __builtin_fma(t, t, s[g]);
-            t = q1 - (double)x[g][c].y; s[g] = __builtin_fma(t, t, s[g]);
-            t = q2 - (double)x[g][c].z; s[g] = __builtin_fma(t, t, s[g]);
-            t = q3 - (double)x[g][c].w; s[g] = __builtin_fma(t, t, s[g]);
+            t = q0 - (double)x.x; s[g] = __builtin_fma(t, t, s[g]);
+            t = q1 - (double)x.y; s[g] = __builtin_fma(t, t, s[g]);
+            t = q2 - (double)x.z; s[g] = __builtin_fma(t, t, s[g]);
+            t = q3 - (double)x.w; s[g] = __builtin_fma(t, t, s[g]);
         }
     }
     d0 = (float)sum8(s[0]);
@@ -384,7 +393,7 @@ __device__ __forceinline__ void eval_group8x2(const XT* __restrict__ X, int dp, 
 // before step i is reduced, so the arithmetic overlaps the memory latency.
 template <int C, typename XT = float>
 struct Gather16 {
-    float4 x[2][C];
+    Row<C, XT> row[2];
     __device__ __forceinline__ void issue(const XT* __restrict__ X, int dp, int cnt, int32_t myid, int sb0) {
         const int lane = lane_id();
         const int sub = lane & 7;
@@ -392,7 +401,7 @@ struct Gather16 {
         for (int g = 0; g < 2; ++g) {
             const int j = sb0 + 8 * g + (lane >> 3);
             const int id = __shfl(myid, (j < cnt ? j : cnt - 1) & 63);
-            load_row<C, XT>(X, dp, id, sub, true, x[g]);
+            row[g].load(X, dp, id, sub);
         }
     }
     __device__ __forceinline__ void consume(const float4 (&qv)[C], int sb0, float& mine) const {
@@ -405,11 +414,12 @@ struct Gather16 {
             const double q0 = qf.x, q1 = qf.y, q2 = qf.z, q3 = qf.w;
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
+                const float4 x = row[g].chunk(c);
                 double t;
-                t = q0 - (double)x[g][c].x; s[g] = __builtin_fma(t, t, s[g]);
-                t = q1 - (double)x[g][c].y; s[g] = __builtin_fma(t, t, s[g]);
-                t = q2 - (double)x[g][c].z; s[g] = __builtin_fma(t, t, s[g]);
-                t = q3 - (double)x[g][c].w; s[g] = __builtin_fma(t, t, s[g]);
+                t = q0 - (double)x.x; s[g] = __builtin_fma(t, t, s[g]);
+                t = q1 - (double)x.y; s[g] = __builtin_fma(t, t, s[g]);
+                t = q2 - (double)x.z; s[g] = __builtin_fma(t, t, s[g]);
+                t = q3 - (double)x.w; s[g] = __builtin_fma(t, t, s[g]);
             }
         }
         const int src = (lane & 7) << 3;
@@ -1004,22 +1014,17 @@ __device__ void traverse_lean(const DevIndex& ix, const SearchLaunch& A, const Q
                     for (int j0 = 0; j0 < ns; j0 += G) {
                         const int j = C > 0 ? j0 + (lane >> 3) : lane;
                         const int32_t id = W.enbuf[j < ns ? j : ns - 1];
-                        // a8; two steps before their keys are inserted when
-                        // more than 8 candidates are fresh (unclustered data
-                        // leaves most of the budget), short rows with both
-                        // steps' loads in flight (fp32 rows of 65 to 128
-                        // values: one step at a time, two made one query
-                        // alone 111 us instead of 105)
+                        // a8; two steps, their loads in flight together, before
+                        // their keys are inserted when more than 8 candidates
+                        // are fresh (unclustered data leaves most of the
+                        // budget).  fp32 rows of 65 to 128 values: one step
+                        // at a time, two made one query alone 111 us instead
+                        // of 105.
                         if constexpr (C > 0 && (C <= 2 || sizeof(XT) == 2)) {
                             if (ns - j0 > 8) {
                                 const int32_t id1 = W.enbuf[j + 8 < ns ? j + 8 : ns - 1];
                                 float d0, d1;
-                                if constexpr (C <= 2) {
-                                    eval_group8x2<C, XT>(rows_of<XT>(ix), ix.dp, Q.qv, id, id1, d0, d1);
-                                } else {
-                                    d0 = Q.template eval_groups<true>(ix, ns, id);
-                                    d1 = Q.template eval_groups<true>(ix, ns, id1);
-                                }
+                                eval_group8x2<C, (C > 2 && LP > 1), XT>(rows_of<XT>(ix), ix.dp, Q.qv, id, id1, d0, d1);
                                 absorb(make_key(d0, id), j);
                                 absorb(make_key(d1, id1), j + 8);
                                 j0 += 8;

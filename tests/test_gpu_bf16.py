@@ -115,3 +115,22 @@ def test_bf16_padded_rows_and_large_scale():
         g_ids, g_d = c.gpu(10, 64, **p)
         o_ids, o_d, _ = c.cpu(10, 64, **p)
         assert_parity(g_ids, g_d, o_ids, o_d)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,L,budget", [(65, 64, 9), (100, 17, 16), (127, 64, 17), (128, 128, 33), (66, 129, 64), (128, 256, 64)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_bf16_many_fresh_candidates(d, L, budget, mode):
+    # unclustered rows of 65 to 128 values leave most of the budget fresh: one
+    # step of 8 candidates, two in flight, and a remainder, at every pool size
+    print(f"[gpu] bf16 rows: unclustered n=4000 d={d} L={L} budget={budget} mode={mode}", flush=True)
+    rng = np.random.default_rng(d)
+    n, nq = 4000, 40
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    attr = rng.permutation(n).astype(np.float64)
+    lo, hi = workloads.ranges_for_selectivity(rng, np.exp2(-4.0 * rng.random(nq)), n)
+    c = BCase(X, attr, rng.standard_normal((nq, d)).astype(np.float32), lo, hi)
+    p = dict(epn=16, entry_mode=mode, budget=budget)
+    g_ids, g_d = c.gpu(10, L, **p)
+    o_ids, o_d, _ = c.cpu(10, L, **p)
+    assert_parity(g_ids, g_d, o_ids, o_d)
