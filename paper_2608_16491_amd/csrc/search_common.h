@@ -867,38 +867,42 @@ __device__ __forceinline__ uint64_t key_at(const uint64_t (&key)[LP], int p) {
         if (LP == 1 || s == (p >> 6)) k = readlane64(key[s], p & 63);
     return k;
 }
-// Insert kj into the sorted keys (np of them, at most L kept): the keys above
-// it move up one lane (a wavefront shift by data-parallel primitives; lane 0
-// of a register takes lane 63 of the one below), and so do the open bits (one
-// per pool entry: not expanded yet), which are wave-uniform.  A key already
-// there, or at or beyond the L-th of a full pool, is dropped.  Keys pushed
-// out stay in the lanes from L on: they are above every key a later insertion
-// counts.
+// Insert kj into the sorted keys (np of them, at most L kept): a position
+// keeps its key if that is below kj, else takes the larger of kj and the key
+// one position down, which a wavefront shift by data-parallel primitives
+// brings (lane 0 of a register takes lane 63 of the one below).  The open
+// bits (one per pool entry: not expanded yet) move with the keys; they are
+// wave-uniform.  A key already there is dropped.  Keys pushed out, or beyond
+// the L-th of a full pool, stay in the lanes from L on: they are above every
+// key a later insertion moves.  No test on a register: the place counted
+// first and each register then left, shifted or split by a branch of its own
+// took longer from 65 entries on than the general merge through LDS (777
+// queries, 100k x 128, L = 128, budget 32: merge 639 us, branches 674, so 560;
+// 100k x 64, L = 256: 789, 822, 724; L = 64: 269, 260, 240).
 template <int LP>
 __device__ __forceinline__ void insert_key(uint64_t (&key)[LP], uint64_t (&open)[LP], int& np, int L, uint64_t kj) {
-    const int lane = lane_id();
-    int c = 0;
+    uint64_t lt[LP], dup = 0;
 #pragma unroll
-    for (int s = 0; s < LP; ++s) c += __popcll(ballot(key[s] < kj));
-    if (c >= L) return;
-    const int cs = c >> 6, cl = c & 63;
-    if (key_at<LP>(key, c) == kj) return;
+    for (int s = 0; s < LP; ++s) {
+        lt[s] = ballot(key[s] < kj);
+        dup |= ballot(key[s] == kj);
+    }
+    if (dup) return;
+    uint64_t in = 0;                      // the key below the register's first position
+    uint64_t in_lt = 1, in_open = 0;      // whether it is below kj; an open bit moving up
 #pragma unroll
-    for (int s = LP - 1; s >= 0; --s) {
-        if (s < cs) continue;
-        // lane 0 of the shifted register (used only above register cs)
-        const uint64_t in = s > 0 ? readlane64(key[s > 0 ? s - 1 : 0], 63) : kj;
+    for (int s = 0; s < LP; ++s) {
+        const uint64_t top = s + 1 < LP ? readlane64(key[s], 63) : 0;
         const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)in, (int)(uint32_t)key[s], 0x138, 0xF, 0xF, false);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(in >> 32), (int)(uint32_t)(key[s] >> 32), 0x138, 0xF, 0xF, false);
         const uint64_t up = ((uint64_t)hi << 32) | lo;
-        if (s > cs) {
-            key[s] = up;
-            open[s] = (open[s] << 1) | (open[s > 0 ? s - 1 : 0] >> 63);
-        } else {
-            key[s] = lane < cl ? key[s] : (lane == cl ? kj : up);
-            const uint64_t below = ((uint64_t)1 << cl) - 1;
-            open[s] = (open[s] & below) | ((open[s] & ~below) << 1) | ((uint64_t)1 << cl);
-        }
+        const uint64_t below = (lt[s] << 1) | in_lt;   // positions whose lower neighbour is below kj
+        key[s] = __builtin_amdgcn_inverse_ballot_w64(lt[s]) ? key[s] : (__builtin_amdgcn_inverse_ballot_w64(below) ? kj : up);
+        const uint64_t moved = open[s] & ~lt[s];
+        open[s] = (open[s] & lt[s]) | (moved << 1) | in_open | (below & ~lt[s]);
+        in = top;
+        in_lt = lt[s] >> 63;
+        in_open = moved >> 63;
     }
     np = np + 1 < L ? np + 1 : L;
 }

@@ -84,3 +84,18 @@ def test_entry_gather_keeps_two_steps_in_flight(probe, rows):
     assert blocks
     for b in blocks:
         assert "LLLL" in b and "Lw" not in b, b
+
+
+@pytest.mark.parametrize("rows,c", [("float", 2), ("float", 4), ("bf16x", 4)])
+@pytest.mark.parametrize("lp", [1, 2, 4])
+def test_insertion_branches_once(traversal, lp, rows, c):
+    # from the head of the innermost loop that shifts the pool to its last
+    # shift: one test, whether the key is there already (lanes masked off by
+    # the moves themselves are no tests)
+    text = traversal[f"s_search_kernel<{c}, {lp}, {rows}, true>"]
+    shifts = [m.start() for m in re.finditer("wave_shr", text)]
+    assert len(shifts) >= 2 * lp
+    heads = [m.start() for m in re.finditer("Inner Loop Header", text) if m.start() < shifts[0]]
+    last = shifts[2 * lp - 1]
+    assert text.count("wave_shr", heads[-1], last) == 2 * lp - 1
+    assert len(re.findall(r"s_cbranch_(?:scc|vcc)", text[heads[-1]:last])) <= 1
