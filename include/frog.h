@@ -260,9 +260,11 @@ int frog_search_ex(const frog_index_t* idx, const float* d_queries, int64_t nq,
  *     must be serialised by the caller.
  *   - A call whose workspace exceeds 256 MiB is refused with FROG_EUNSUPPORTED
  *     before anything is enqueued.  Roughly: entry_mode 0 needs 12 bytes per
- *     query plus, when the entry count exceeds one 768-point chunk,
- *     512 * ceil(L/64) bytes per chunk (about 2 KB per query at 2,560 entry
- *     points and L <= 64); entry_mode 1 at n = 1M about 13.5 KB per query at
+ *     query plus, when a query's entry points make more than one chunk, 512
+ *     bytes (L <= 64), 1,024 (L <= 128) or 2,048 per chunk: chunks of 768 (about
+ *     2 KB per query at 2,560 entry points and L <= 64), and in small batches
+ *     (at most a few queries per CU) four chunks per query from 65 entry
+ *     points on, under 4 MB in all; entry_mode 1 at n = 1M about 13.5 KB per query at
  *     L <= 40 (about 19,700 queries per call), 17.6 KB up to L = 56, 34.5 KB
  *     up to L = 120 and 35 KB up to L = 256, plus about 2 MB; the exact
  *     visited set (hash_log2 = 0) adds n/8 bytes per resident wavefront and

@@ -22,7 +22,8 @@ namespace {
 // workgroup share queries: a 64-bit LDS word holds the workgroup's open query
 // and the next unclaimed entry chunk (claimed by compare-and-swap); a wave
 // that finds the open query exhausted opens the next one from the global
-// counter.  A wave evaluates one chunk (512 entry points) into a pool, writes
+// counter.  A wave evaluates one chunk (FROG_CHUNK entry points, a quarter of
+// the query's in small batches) into a pool, writes
 // it to global memory and counts the query's finished chunks with a
 // workgroup-scope atomic; the wave that finishes the last chunk merges the
 // chunk pools (the L nearest entry points) and runs the query's traversal,
@@ -274,19 +275,29 @@ int launch_search_ws(const DevIndex& ix, const SearchLaunch& a, void* stream_v, 
     int64_t chunk = FROG_CHUNK;
     if ((emax + chunk - 1) / chunk > 16) chunk = ((emax + 15) / 16 + 15) / 16 * 16;
     int cpq = (int)((emax + chunk - 1) / chunk);
-    // few queries (a workgroup each, and then some to spare): about four
-    // chunks per query, one for each wavefront of its workgroup.  Larger
-    // batches keep the long chunks, whose pools cost fewer merges (1,004
-    // queries of 970 entry points, 14k x 20: 186 us with chunks of 768, 191
-    // us with 256)
+    // few queries: about four chunks per query, one for each wavefront of its
+    // workgroup; larger batches keep the long chunks, whose pools cost fewer
+    // merges.  The line lies at a query per CU for pools of 256 or rows of 32
+    // values, where the merges weigh most, at two otherwise, at three for
+    // pools of 64 over rows above 128 values (three long chunks become four at
+    // any size the wavefronts allow).  Four chunks against one, 200 to 1,536
+    // entry points: L = 256, 256 queries 1.02 to 1.23 times as fast, 384
+    // to 768 queries 0.95 to 1.07, then 0.79 to 0.98; L = 128, 128 values, 512
+    // queries 0.97 to 1.06, 1,000 0.91 to 0.97; L = 32, 960 values, 768 queries
+    // 0.97 to 1.14; L = 32, 32 values, 256 queries 0.93 to 1.07, 512 0.96 to 1.02,
+    // 1,000 0.91 to 0.96.
+    int cus = 0, dev = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int lp = lp_of(a.L);
+    const int per_cu = lp == 4 || ix.dp <= 32 ? 1 : (lp == 1 && ix.dp > 128 ? 3 : 2);
     const int64_t waves = (int64_t)max_blocks((const void*)fn, smem) * kWavesPerBlock;
-    if (a.hash_log2 > 0 && a.nq * cpq <= waves / 4 && cpq < 4) {
+    if (a.hash_log2 > 0 && cpq < 4 && a.nq * cpq <= waves / 4 && (cpq == 3 || a.nq <= (int64_t)per_cu * cus)) {
         chunk = ((emax + 3) / 4 + 15) / 16 * 16;
         chunk = chunk < 64 ? 64 : chunk;
         cpq = (int)((emax + chunk - 1) / chunk);
     }
     if (a.nq >= ((int64_t)1 << 31) - 1) return fail(FROG_EINVAL, "nq=%lld too large", (long long)a.nq);
-    const int lp = lp_of(a.L);
     int blocks = max_blocks((const void*)fn, smem);
     const int64_t need = (a.nq * cpq + kWavesPerBlock - 1) / kWavesPerBlock;
     if (need < blocks) blocks = (int)need;

@@ -243,3 +243,25 @@ def test_lean_traversal_pool_edges(tiny, L, budget, mode):
         g_ids, g_d = tiny.gpu(10, L, hash_log2=h, **p)
         o_ids, o_d, _ = tiny.cpu(10, L, **p)
         assert_parity(g_ids, g_d, o_ids, o_d)
+
+
+@pytest.mark.parametrize("nq", [3, 255, 257, 511, 513, 769])
+@pytest.mark.parametrize("L", [32, 100, 200])
+def test_entry_chunks_of_small_batches(nq, L):
+    # batches around one, two and three queries per CU, whose entry points are
+    # cut into four chunks (64 at least) or into chunks of 768
+    print(f"[gpu] entry chunks: n=6000 d=64 nq={nq} L={L}", flush=True)
+    rng = np.random.default_rng(nq)
+    n = 6000
+    X = rng.standard_normal((n, 64)).astype(np.float32)
+    lo, hi = workloads.ranges_for_selectivity(rng, np.exp2(-5.0 * rng.random(nq)), n)
+    ix = F.Index.build(X, rng.permutation(n).astype(np.float64), device=0)
+    e = ix.export()
+    ox = oracle.OracleIndex(e["perm"], e["attr_sorted"], e["X_rank"], e["ENC"])
+    Q = rng.standard_normal((nq, 64)).astype(np.float32)
+    dQ, dlo, dhi = _cuda(Q, torch.float32), _cuda(lo, torch.float64), _cuda(hi, torch.float64)
+    for emax in (65, 500, 768, 1000, 2300, 2310):
+        ids, ds = F.search(ix, dQ, dlo, dhi, 10, L, epn=16, epn_frac=1.0, epn_max=emax)
+        o_ids, o_d, _ = oracle.search(ox, Q, np.asarray(lo, np.float64), np.asarray(hi, np.float64), 10, L, qidx=np.arange(nq),
+                                      epn=16, epn_frac=1.0, epn_max=emax, B=16)
+        assert_parity(ids.cpu().numpy(), ds.cpu().numpy(), o_ids, o_d)
