@@ -28,9 +28,12 @@
 //      last threshold or the K'-th value kept; if that minus the approximation
 //      bound exceeds the k-th exact distance, the result is certified exact
 //      (reported per query).
-//   4. Queries the margin test leaves uncertified (near-tied distances that
+//   4. Queries whose list overflowed, because the rows follow a pattern in rank
+//      order that the sampled blocks are in step with, go through 1 to 3 once
+//      more with sampled blocks drawn by a hash.
+//   5. Queries the margin test leaves uncertified (near-tied distances that
 //      the fp32 approximation cannot separate, e.g. vectors with large norms
-//      close to each other; or a list that overflowed) are recomputed
+//      close to each other; or more ties than a list holds) are recomputed
 //      exhaustively: every rank of the interval with the exact canonical
 //      distance (launch_exact_ranges), so every returned row is the exact
 //      filtered k-NN.
@@ -45,6 +48,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -80,6 +84,7 @@ struct BMeta {
     unsigned long long rows;      // rows of all tiles' unions
     uint32_t places;              // places in the order, a multiple of kBQ
     uint32_t nfail;               // uncertified queries
+    uint32_t nredo;               // queries to be scanned again
     uint32_t counter[kBPasses];   // work counters of the passes
     uint32_t nitems[kBPasses];
     int64_t chunk[kBPasses];      // rows per work item of each pass
@@ -96,7 +101,8 @@ struct BFParams {
     int cap;              // entries per query's list
     int64_t tmax;         // tiles at most
     int64_t imax;         // work items at most
-    int npass;            // pass p scans every 16^p-th block
+    int npass;            // pass p scans every 16^p-th block, or one drawn of each 16^p
+    bool again;           // the second time, for the queries marked in redo
     BMeta* meta;
     uint32_t* hist;       // [kBBands kBBins] queries per bucket, then the bucket's first place
     int32_t* lr;          // [nq][2] rank intervals
@@ -109,6 +115,7 @@ struct BFParams {
     uint64_t* list;       // [nq][cap] (orderable bits of the approximate distance << 32 | row)
     int32_t* cnt;         // [nq] entries offered to the list (more than cap: it overflowed)
     float* thr;           // [nq] rows at or above it are not listed
+    int32_t* redo;        // [nq] 1: the list overflowed, to be scanned again
     int32_t* fail;        // [nq][3] uncertified queries: index, l, r
     int32_t* ids;
     float* dists;
@@ -121,7 +128,7 @@ __global__ void bf_init_kernel(BFParams P) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) {
         P.meta->rows = 0ull;
-        P.meta->nfail = 0u;
+        if (!P.again) P.meta->nfail = P.meta->nredo = 0u;
         for (int p = 0; p < kBPasses; ++p) P.meta->counter[p] = 0u;
     }
     if (i < kBBands * kBBins) P.hist[i] = 0u;
@@ -129,6 +136,7 @@ __global__ void bf_init_kernel(BFParams P) {
     if (i < P.nq) {
         P.cnt[i] = 0;
         P.thr[i] = __int_as_float(0x7f800000);
+        if (!P.again) P.redo[i] = 0;
     }
 }
 
@@ -136,7 +144,7 @@ __global__ void bf_init_kernel(BFParams P) {
 // (octave of the range size, l); the padded row of an empty range.
 __global__ __launch_bounds__(kBlock) void bf_plan_kernel(BFParams P) {
     const int64_t q = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (q >= P.nq) return;   // wave-uniform
+    if (q >= P.nq || (P.again && P.redo[q] == 0)) return;   // wave-uniform
     const int lane = lane_id();
     int64_t l, r;
     rank_interval(P.ix, P.lo[q], P.hi[q], l, r);
@@ -197,7 +205,7 @@ __global__ __launch_bounds__(1024) void bf_bins_kernel(BFParams P) {
 
 __global__ void bf_order_kernel(BFParams P) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= P.nq || P.lr[2 * q] > P.lr[2 * q + 1]) return;
+    if (q >= P.nq || P.lr[2 * q] > P.lr[2 * q + 1] || (P.again && P.redo[q] == 0)) return;
     P.order[P.hist[P.bucket[q]] + P.place[q]] = (int32_t)q;
 }
 
@@ -305,16 +313,52 @@ __global__ __launch_bounds__(1024) void bf_items_kernel(BFParams P) {
 // ------------------------------------------------------------------ scan
 
 // The blocks (16 rows, block b = rows 16 b ..) of a pass: the multiples of
-// 2^sh; but16: those of 2^(sh + 4), which an earlier pass scanned, left out.
-__device__ __forceinline__ int32_t first_block(int sh, bool but16, int32_t b) {
-    int32_t m = (b + (1 << sh) - 1) >> sh;
-    if (but16 && (m & 15) == 0) ++m;
-    return m << sh;
-}
-__device__ __forceinline__ int32_t next_block(int sh, bool but16, int32_t b) {
-    b += 1 << sh;
-    return but16 && ((b >> sh) & 15) == 0 ? b + (1 << sh) : b;
-}
+// 16^pass; but16: those of 16^(pass + 1), which an earlier pass scanned, left
+// out.  DRAWN: in place of every 16th element of a pass the next coarser one
+// takes one of each 16, drawn by a hash, so that no pattern of the rows is in
+// step with them (it costs the scan 1 to 3 % more scalar work per block, so
+// only queries that need it pay: 4,000 queries of 300k x 128 whose every 16th
+// block of rows lies far away took 14.9 ms when the 2,829 lists that overflowed
+// went to the exact pass at once, 2.6 ms so).
+template <bool DRAWN>
+struct Blocks {
+    int pass;
+    bool but16;
+    // the drawn one of elements 16 g .. 16 g + 15 of pass p
+    __device__ static __forceinline__ int32_t drawn(int32_t g, int p) {
+        uint32_t x = ((uint32_t)g + ((uint32_t)p << 28)) * 0x9E3779B1u;
+        x = (x ^ (x >> 15)) * 0x85EBCA77u;
+        return 16 * g + (int32_t)(x >> 28);
+    }
+    // DRAWN: the block of element m (in [m, m + 1) 16^pass), and of the first
+    // element from m on that the pass scans
+    __device__ __forceinline__ int32_t block(int32_t m) const {
+        for (int p = pass - 1; p >= 0; --p) m = drawn(m, p);
+        return m;
+    }
+    __device__ __forceinline__ int32_t from(int32_t m) const {
+        while (but16 && m == drawn(m >> 4, pass)) ++m;
+        return block(m);
+    }
+    // the first block of the pass at or behind b
+    __device__ __forceinline__ int32_t first(int32_t b) const {
+        const int sh = 4 * pass;
+        if constexpr (DRAWN) {
+            const int32_t m = b >> sh;
+            return from(block(m) < b ? m + 1 : m);
+        }
+        int32_t m = (b + (1 << sh) - 1) >> sh;
+        if (but16 && (m & 15) == 0) ++m;
+        return m << sh;
+    }
+    // the one behind block b of the pass
+    __device__ __forceinline__ int32_t next(int32_t b) const {
+        const int sh = 4 * pass;
+        if constexpr (DRAWN) return from((b >> sh) + 1);
+        b += 1 << sh;
+        return but16 && ((b >> sh) & 15) == 0 ? b + (1 << sh) : b;
+    }
+};
 
 // One wavefront, persistent: takes work items of the pass.  KT = dp / 16
 // float4 chunks of the 32 queries' operand in registers (d <= 128: at d = 128
@@ -330,10 +374,10 @@ __device__ __forceinline__ int32_t next_block(int sh, bool but16, int32_t b) {
 // took 0.86 ms (its loads wait for the products to have read the buffer).
 // Work items grouped by XCD, a raised priority during the products and four
 // accumulation chains changed nothing.
-template <int KT>
+template <int KT, bool DRAWN>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KT > 4 || KT == 0 ? 2 : 3)))
 void bf_scan_kernel(BFParams P, int pass, bool but16) {
-    const int sh = 4 * pass;
+    const Blocks<DRAWN> S{pass, but16};
     __shared__ uint64_t s_key[kBBuf];
     __shared__ uint8_t s_slot[kBBuf];
     __shared__ uint16_t s_off[kBBuf];
@@ -381,7 +425,7 @@ void bf_scan_kernel(BFParams P, int pass, bool but16) {
         const int64_t row0 = c0 > T.ul ? c0 : T.ul;
         const int64_t row1 = c0 + chunk - 1 < T.ur ? c0 + chunk - 1 : T.ur;
         const int32_t bend = (int32_t)(row1 >> 4);
-        int32_t b = first_block(sh, but16, (int32_t)(row0 >> 4));
+        int32_t b = S.first((int32_t)(row0 >> 4));
         if (b > bend) continue;
         if (lane < kBQ) {
             s_q[lane] = T.q[lane];
@@ -507,11 +551,11 @@ void bf_scan_kernel(BFParams P, int pass, bool but16) {
             float4 xa[KT], xb[KT];
             load_rows(b, xa);
             for (;;) {
-                int32_t nb = next_block(sh, but16, b);
+                const int32_t nb = S.next(b);
                 load_rows(nb <= bend ? nb : b, xb);
                 process(b, xa);
                 if (nb > bend) break;
-                b = next_block(sh, but16, nb);
+                b = S.next(nb);
                 load_rows(b <= bend ? b : nb, xa);
                 process(nb, xb);
                 if (b > bend) break;
@@ -523,7 +567,7 @@ void bf_scan_kernel(BFParams P, int pass, bool but16) {
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
                     blk[i] = b;
-                    b = next_block(sh, but16, b);
+                    b = S.next(b);
                     const int32_t at = (blk[i] <= bend ? blk[i] : bend) * 16 + ii;
                     const int64_t row = at < n32 ? at : n32 - 1;
                     xr[i] = X4 + row * dp4 + kk;
@@ -658,6 +702,7 @@ __global__ __launch_bounds__(64) void bf_merge_kernel(BFParams P) {
     const DevIndex& ix = P.ix;
     const int64_t l = uniform(P.lr[2 * q]), r = uniform(P.lr[2 * q + 1]);
     if (l > r) return;   // padded by bf_plan_kernel
+    if (P.again && uniform(P.redo[q]) == 0) return;   // its result stands
     const float* qrow = P.Q + q * ix.d;
     float4 qv[C > 0 ? C : 1];
     if constexpr (C > 0) {
@@ -672,6 +717,29 @@ __global__ __launch_bounds__(64) void bf_merge_kernel(BFParams P) {
     }
     const int f0 = uniform(P.cnt[q]);
     bool ok = f0 <= P.cap;
+    if (!ok && !P.again) {
+        // overflowed: to be scanned again, unless most of the list is tied at
+        // its largest value, which another sample would not change
+        const uint64_t* L = P.list + q * P.cap;
+        uint32_t vmin = 0xFFFFFFFFu, vmax = 0u;
+        for (int i = lane; i < P.cap; i += 64) {
+            const uint32_t v = (uint32_t)(L[i] >> 32);
+            vmin = v < vmin ? v : vmin;
+            vmax = v > vmax ? v : vmax;
+        }
+        wave_minmax_u32(vmin, vmax);
+        int tied = 0;
+        for (int i = lane; i < P.cap; i += 64) tied += (uint32_t)(L[i] >> 32) == vmax ? 1 : 0;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) tied += __shfl_xor(tied, o);
+        if (2 * tied < P.cap) {
+            if (lane == 0) {
+                P.redo[q] = 1;
+                atomicAdd(&P.meta->nredo, 1u);
+            }
+            return;
+        }
+    }
     Pool<LP> pool;
 #pragma unroll
     for (int s = 0; s < LP; ++s) { pool.key[s] = kEmpty; pool.flag[s] = 0u; }
@@ -769,13 +837,14 @@ void (*pick_bf_merge(int dp, int k))(BFParams) {
     }
 }
 
+template <bool DRAWN>
 void (*pick_bf_scan(int dp))(BFParams, int, bool) {
     switch (dp) {
-        case 32: return bf_scan_kernel<2>;
-        case 64: return bf_scan_kernel<4>;
-        case 96: return bf_scan_kernel<6>;
-        case 128: return bf_scan_kernel<8>;
-        default: return bf_scan_kernel<0>;
+        case 32: return bf_scan_kernel<2, DRAWN>;
+        case 64: return bf_scan_kernel<4, DRAWN>;
+        case 96: return bf_scan_kernel<6, DRAWN>;
+        case 128: return bf_scan_kernel<8, DRAWN>;
+        default: return bf_scan_kernel<0, DRAWN>;
     }
 }
 
@@ -818,6 +887,7 @@ int bruteforce_batch(const frog_index* ix, const float* Q, int64_t nq, const dou
     const size_t o_list = take((size_t)nq * P.cap * 8);
     const size_t o_cnt = take((size_t)nq * 4);
     const size_t o_thr = take((size_t)nq * 4);
+    const size_t o_redo = take((size_t)nq * 4);
     const size_t o_fail = take((size_t)nq * 12);
     void* ws = nullptr;
     hipError_t e = ws_alloc(&ws, off, stream);
@@ -835,36 +905,44 @@ int bruteforce_batch(const frog_index* ix, const float* Q, int64_t nq, const dou
     P.list = reinterpret_cast<uint64_t*>(base + o_list);
     P.cnt = reinterpret_cast<int32_t*>(base + o_cnt);
     P.thr = reinterpret_cast<float*>(base + o_thr);
+    P.redo = reinterpret_cast<int32_t*>(base + o_redo);
     P.fail = reinterpret_cast<int32_t*>(base + o_fail);
     P.ids = ids;
     P.dists = dists;
     P.cert = cert;
     const int64_t ninit = std::max<int64_t>(std::max<int64_t>(kBBands * kBBins, P.tmax * kBQ), nq);
     const unsigned qwaves = (unsigned)((nq + kWavesPerBlock - 1) / kWavesPerBlock);
-    hipLaunchKernelGGL(bf_init_kernel, dim3((unsigned)((ninit + 255) / 256)), dim3(256), 0, stream, P);
-    hipLaunchKernelGGL(bf_plan_kernel, dim3(qwaves), dim3(kBlock), 0, stream, P);
-    hipLaunchKernelGGL(bf_bins_kernel, dim3(1), dim3(1024), 0, stream, P);
-    hipLaunchKernelGGL(bf_order_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, stream, P);
-    hipLaunchKernelGGL(bf_tile_kernel, dim3((unsigned)((P.tmax + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock), 0,
-                       stream, P);
-    hipLaunchKernelGGL(bf_items_kernel, dim3((unsigned)P.npass), dim3(1024), 0, stream, P);
-    auto scan = pick_bf_scan(dix.dp);
-    const int blocks = max_blocks((const void*)scan, 0, 64);
-    // The thresholds' places in the sampled lists: about 16 j of the rows the
-    // next pass scans lie below the j-th smallest, with a spread of
-    // 1/sqrt(j); the last list is then about 4 K' long.
-    for (int p = P.npass - 1; p >= 0; --p) {
-        hipLaunchKernelGGL(scan, dim3(blocks), dim3(64), 0, stream, P, p, p < P.npass - 1);
-        if (p > 0)
-            hipLaunchKernelGGL(bf_select_kernel, dim3((unsigned)nq), dim3(64), (size_t)P.cap * 4, stream, P,
-                               p > 1 ? mk / 8 : mk / 4);
+    // {uncertified, to be scanned again}, read back after each time
+    static_assert(offsetof(BMeta, nredo) == offsetof(BMeta, nfail) + 4, "read together");
+    uint32_t left[2] = {0, 0};
+    hipError_t es = hipSuccess;
+    for (int time = 0; time < 2; ++time) {
+        P.again = time > 0;
+        hipLaunchKernelGGL(bf_init_kernel, dim3((unsigned)((ninit + 255) / 256)), dim3(256), 0, stream, P);
+        hipLaunchKernelGGL(bf_plan_kernel, dim3(qwaves), dim3(kBlock), 0, stream, P);
+        hipLaunchKernelGGL(bf_bins_kernel, dim3(1), dim3(1024), 0, stream, P);
+        hipLaunchKernelGGL(bf_order_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, stream, P);
+        hipLaunchKernelGGL(bf_tile_kernel, dim3((unsigned)((P.tmax + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock), 0,
+                           stream, P);
+        hipLaunchKernelGGL(bf_items_kernel, dim3((unsigned)P.npass), dim3(1024), 0, stream, P);
+        auto scan = P.again ? pick_bf_scan<true>(dix.dp) : pick_bf_scan<false>(dix.dp);
+        const int blocks = max_blocks((const void*)scan, 0, 64);
+        // The thresholds' places in the sampled lists: about 16 j of the rows the
+        // next pass scans lie below the j-th smallest, with a spread of
+        // 1/sqrt(j); the last list is then about 4 K' long.
+        for (int p = P.npass - 1; p >= 0; --p) {
+            hipLaunchKernelGGL(scan, dim3(blocks), dim3(64), 0, stream, P, p, p < P.npass - 1);
+            if (p > 0)
+                hipLaunchKernelGGL(bf_select_kernel, dim3((unsigned)nq), dim3(64), (size_t)P.cap * 4, stream, P,
+                                   p > 1 ? mk / 8 : mk / 4);
+        }
+        hipLaunchKernelGGL(pick_bf_merge(dix.dp, k), dim3((unsigned)nq), dim3(64), 0, stream, P);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(left, &P.meta->nfail, 8, hipMemcpyDeviceToHost, stream);
+        es = hipStreamSynchronize(stream);
+        if (e != hipSuccess || es != hipSuccess || left[1] == 0) break;
     }
-    hipLaunchKernelGGL(pick_bf_merge(dix.dp, k), dim3((unsigned)nq), dim3(64), 0, stream, P);
-    e = hipGetLastError();
-    // the queries the margin test could not certify
-    uint32_t nf = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&nf, &P.meta->nfail, 4, hipMemcpyDeviceToHost, stream);
-    hipError_t es = hipStreamSynchronize(stream);
+    const uint32_t nf = left[0];
     std::vector<int32_t> ff, fq, flr;
     if (e == hipSuccess && es == hipSuccess && nf > 0) {
         ff.resize((size_t)nf * 3);

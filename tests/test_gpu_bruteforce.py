@@ -122,22 +122,40 @@ def test_bruteforce_sampling_passes(n, d, nq, k):
 
 
 @pytest.mark.parametrize("near", [False, True])
-def test_bruteforce_misleading_sample(near):
-    # the rows of the sampled blocks (every 16th block of 16 ranks) lie all
-    # nearer to the queries than the others, or all farther: then the
-    # threshold they give lets every other row into the list, which
-    # overflows, and the exact pass has to give the result
-    print(f"[gpu] bruteforce, sampled rows nearer={near}", flush=True)
+@pytest.mark.parametrize("period", [16, 256])
+def test_bruteforce_rows_in_a_pattern(period, near):
+    # one block of 16 ranks in each 16 or 256 lies nearer to the queries than the
+    # others, or farther: a sample in step with the pattern would give
+    # thresholds that let every other row into the list, which overflows and
+    # leaves the query to the exact pass (slow); a drawn one certifies them all
+    print(f"[gpu] bruteforce, one block of {period} nearer={near}", flush=True)
     rng = np.random.default_rng(5)
     n, d, nq, k = 20000, 24, 40, 10
     X = rng.standard_normal((n, d)).astype(np.float32)
-    sampled = (np.arange(n) // 16) % 16 == 0
-    X[sampled != near] += 6.0      # the others, or the sampled ones, far away
+    odd = (np.arange(n) // 16) % period == 0
+    X[odd != near] += 6.0      # the others, or those blocks, far away
     attr = np.arange(n, dtype=np.float64)
     Q = rng.standard_normal((nq, d)).astype(np.float32)
     cnt = np.array([n, 12000, 300, 40] * (nq // 4))
     lo = rng.integers(0, n - cnt + 1).astype(np.float64)
     hi = lo + cnt - 1
     ids, ds, cert, o_ids, o_d = _run(X, attr, Q, lo, hi, k)
-    assert np.isin(cert, (1, 2)).all()
+    assert (cert == 1).all()
+    assert_parity(ids, ds, o_ids, o_d, max_residual=0)
+
+
+def test_bruteforce_overflowing_list():
+    # 5,000 rows at one distance, the smallest: every threshold lets them all
+    # into the list (2,048 entries), so the exact pass answers, ties by rank
+    print("[gpu] bruteforce, 5000 equal rows", flush=True)
+    rng = np.random.default_rng(6)
+    n, d, nq, k = 20000, 24, 8, 10
+    X = rng.standard_normal((n, d)).astype(np.float32) + 4.0
+    X[rng.permutation(n)[:5000]] = 0.5
+    attr = rng.permutation(n).astype(np.float64)
+    Q = (0.1 * rng.standard_normal((nq, d))).astype(np.float32)
+    lo, hi = np.zeros(nq), np.full(nq, n - 1.0)
+    hi[::2] = n // 40      # 125 or so of them: certified
+    ids, ds, cert, o_ids, o_d = _run(X, attr, Q, lo, hi, k)
+    assert (cert[1::2] == 2).all()
     assert_parity(ids, ds, o_ids, o_d, max_residual=0)
