@@ -284,7 +284,11 @@ int frog_search_noalloc(const frog_index_t* idx, const float* d_queries, int64_t
  * d_certified (NULL or nq int32) tells how each row was obtained: 1 = by the
  * margin test (or an empty range), 2 = by the exhaustive exact pass.  The
  * queries left to that pass are read back to the host, so this call
- * synchronises `stream`; it is a ground-truth tool, not the search path. */
+ * synchronises `stream`; it is a ground-truth tool, not the search path.
+ * Large batches are done in parts, each with a workspace of at most about 0.3
+ * GB whatever k (256 MiB of lists: 16 KB a query at k <= 64, 32 at k <= 128,
+ * 64 above; and the padded queries), less where the device has no such room; the library's pool
+ * keeps it for later calls. */
 int frog_bruteforce_filtered(const frog_index_t* idx, const float* d_queries, int64_t nq,
                              const double* d_lo, const double* d_hi, int k,
                              int32_t* d_ids, float* d_dists, int32_t* d_certified,

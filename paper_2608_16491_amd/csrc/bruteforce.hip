@@ -67,7 +67,8 @@ constexpr int kBG = 4096;        // chunks of rows at most
 constexpr int kBItems = 16384;   // work items of the last pass at most (and up to two more per tile)
 constexpr int kBBuf = 1024;      // candidates a wavefront buffers in LDS
 constexpr int kBPasses = 7;      // at most: 2^31 rows sampled down to 16^6 times fewer
-constexpr int64_t kBBatch = 16384;   // queries planned at a time (bounds the workspace)
+constexpr int64_t kBBatch = 16384;   // queries planned at a time at most
+constexpr int64_t kBBytes = (int64_t)256 << 20;   // their lists at most
 constexpr int kBTiles = (int)(kBBatch / kBQ) + kBBands;   // tiles at most
 static_assert(kBTiles <= 1024, "one thread per tile");
 
@@ -848,13 +849,16 @@ void (*pick_bf_scan(int dp))(BFParams, int, bool) {
     }
 }
 
+// entries re-ranked per query, as bf_merge_kernel's instances, and per list
+int bf_kept(int k) { return k <= 32 ? 64 : (k <= 64 ? 128 : (k <= 128 ? 256 : 512)); }
+int bf_cap(int k) { return std::max(2048, 16 * bf_kept(k)); }
+
 // One batch of at most kBBatch queries.
 int bruteforce_batch(const frog_index* ix, const float* Q, int64_t nq, const double* lo, const double* hi, int k,
                      int32_t* ids, float* dists, int32_t* cert, hipStream_t stream) {
     const DevIndex dix{ix->dX, ix->dXh, ix->dENC, ix->dattr, ix->dperm, ix->n, ix->d, ix->dp, ix->H, ix->m,
                        ix->storage};
-    // entries re-ranked per query, as bf_merge_kernel's instances
-    const int mk = k <= 32 ? 64 : (k <= 64 ? 128 : (k <= 128 ? 256 : 512));
+    const int mk = bf_kept(k);
     BFParams P{};
     P.ix = dix;
     P.Q = Q;
@@ -863,7 +867,7 @@ int bruteforce_batch(const frog_index* ix, const float* Q, int64_t nq, const dou
     P.nq = nq;
     P.k = k;
     P.maxnorm = ix->maxnorm;
-    P.cap = std::max(2048, 16 * mk);
+    P.cap = bf_cap(k);
     // the first pass lists every row it scans: at most 3/4 of the cap
     P.npass = 1;
     while (P.npass < kBPasses && (dix.n >> (4 * (P.npass - 1))) > P.cap * 3 / 4) ++P.npass;
@@ -891,7 +895,10 @@ int bruteforce_batch(const frog_index* ix, const float* Q, int64_t nq, const dou
     const size_t o_fail = take((size_t)nq * 12);
     void* ws = nullptr;
     hipError_t e = ws_alloc(&ws, off, stream);
-    if (e != hipSuccess) return fail(FROG_ENOMEM, "bruteforce workspace: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();   // not to be reported by the next launch
+        return fail(FROG_ENOMEM, "bruteforce workspace: %s", hipGetErrorString(e));
+    }
     char* base = reinterpret_cast<char*>(ws);
     P.meta = reinterpret_cast<BMeta*>(base + o_meta);
     P.hist = reinterpret_cast<uint32_t*>(base + o_hist);
@@ -966,11 +973,23 @@ int bruteforce_batch(const frog_index* ix, const float* Q, int64_t nq, const dou
 
 int launch_bruteforce(const frog_index* ix, const float* Q, int64_t nq, const double* lo,
                       const double* hi, int k, int32_t* ids, float* dists, int32_t* cert, void* stream_v) {
-    for (int64_t q0 = 0; q0 < nq; q0 += kBBatch) {
-        const int64_t c = std::min(kBBatch, nq - q0);
+    // equal batches whose lists (16 KB a query at k <= 64, 32 at k <= 128, 64
+    // above) fit kBBytes, and smaller ones on a device that has no such room
+    // left (16,384 queries of 300k x 64, k = 256: 1.07 GB in one batch and
+    // 3.2 ms, 4.7 in four; k <= 64 as before)
+    const int64_t most = std::min(kBBatch, kBBytes / (8 * (int64_t)bf_cap(k)));
+    const int64_t parts = (nq + most - 1) / most;
+    int64_t batch = parts > 1 ? ((nq + parts - 1) / parts + kBQ - 1) / kBQ * kBQ : nq;
+    for (int64_t q0 = 0; q0 < nq;) {
+        const int64_t c = std::min(batch, nq - q0);
         const int rc = bruteforce_batch(ix, Q + q0 * ix->d, c, lo + q0, hi + q0, k, ids + q0 * k, dists + q0 * k,
                                         cert ? cert + q0 : nullptr, (hipStream_t)stream_v);
+        if (rc == FROG_ENOMEM && c > 256) {
+            batch = (c / 2 + kBQ - 1) / kBQ * kBQ;
+            continue;
+        }
         if (rc != FROG_OK) return rc;
+        q0 += c;
     }
     return FROG_OK;
 }

@@ -150,7 +150,10 @@ int launch_exact_ranges(const DevIndex& ix, const float* Q, const int32_t* hq, c
     const size_t bytes = o_part + (size_t)nitems * 64 * lp * 8;
     void* ws = nullptr;
     hipError_t e = ws_alloc(&ws, bytes, stream);
-    if (e != hipSuccess) return fail(FROG_ENOMEM, "exact ranges workspace: %s", hipGetErrorString(e));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();   // not to be reported by the next launch
+        return fail(FROG_ENOMEM, "exact ranges workspace: %s", hipGetErrorString(e));
+    }
     char* base = reinterpret_cast<char*>(ws);
     XParams P{};
     P.ix = ix;

@@ -159,3 +159,30 @@ def test_bruteforce_overflowing_list():
     ids, ds, cert, o_ids, o_d = _run(X, attr, Q, lo, hi, k)
     assert (cert[1::2] == 2).all()
     assert_parity(ids, ds, o_ids, o_d, max_residual=0)
+
+
+def test_bruteforce_workspace_is_bounded():
+    # the largest k has lists four times as long as the smallest: a batch
+    # of any size is done in parts that take at most about 0.3 GB, which the
+    # pool keeps (1.07 GB at once before); rows on both sides of the parts' ends
+    print("[gpu] bruteforce workspace: n=3000 d=32 nq=16384 k=256", flush=True)
+    rng = np.random.default_rng(7)
+    n, d, nq, k = 3000, 32, 16384, 256
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    attr = rng.permutation(n).astype(np.float64)
+    Q = rng.standard_normal((nq, d)).astype(np.float32)
+    lo, hi = workloads.ranges_for_selectivity(rng, np.exp2(-3.0 * rng.random(nq)), n)
+    perm = np.argsort(attr, kind="stable").astype(np.int32)
+    ix = F.Index.from_arrays(X[perm], attr[perm], perm, -np.ones((n, 1, 1), np.int32)).upload(0)
+    dQ, dlo, dhi = _cuda(Q, torch.float32), _cuda(lo, torch.float64), _cuda(hi, torch.float64)
+    F.bruteforce(ix, dQ[:32], dlo[:32], dhi[:32], k)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    ids, ds, cert = F.bruteforce(ix, dQ, dlo, dhi, k)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 400 << 20    # 34 MB of it the results
+    for s in (0, 4032, 8064, 12096, 16352):
+        rows = slice(s, s + 32)
+        o_ids, o_d = oracle.exact(X[perm], attr[perm], perm, Q[rows], lo[rows], hi[rows], k)
+        assert_parity(ids[rows].cpu().numpy(), ds[rows].cpu().numpy(), o_ids, o_d, max_residual=0)
