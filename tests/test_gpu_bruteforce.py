@@ -186,3 +186,23 @@ def test_bruteforce_workspace_is_bounded():
         rows = slice(s, s + 32)
         o_ids, o_d = oracle.exact(X[perm], attr[perm], perm, Q[rows], lo[rows], hi[rows], k)
         assert_parity(ids[rows].cpu().numpy(), ds[rows].cpu().numpy(), o_ids, o_d, max_residual=0)
+
+
+@pytest.mark.parametrize("d", [129, 960])
+@pytest.mark.parametrize("nq", [1, 16, 17, 32, 45])
+def test_bruteforce_wide_rows_half_tiles(d, nq):
+    # rows above 128 values multiply only the halves of a tile of 32 queries
+    # that hold queries near the blocks: batches that fill one half, both, and
+    # spill into a second tile; short ranges far apart, so that most blocks meet
+    # the intervals of one half or of none
+    print(f"[gpu] bruteforce wide rows, half tiles d={d} nq={nq}", flush=True)
+    rng = np.random.default_rng(d + nq)
+    n = 5000
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    attr = rng.permutation(n).astype(np.float64)
+    Q = rng.standard_normal((nq, d)).astype(np.float32)
+    for cnt in (n, 300, 40):
+        lo = rng.integers(0, n - cnt + 1, nq).astype(np.float64)
+        ids, ds, cert, o_ids, o_d = _run(X, attr, Q, lo, lo + cnt - 1, 10)
+        assert (cert == 1).all()
+        assert_parity(ids, ds, o_ids, o_d, max_residual=0)
