@@ -170,12 +170,12 @@ void coop_kernel(KParams P) {
         }
         if constexpr (LEAN) {
             traverse_lean<C, LP, XT>(P.ix, P.a, Q, pool, W, vis);
-            continue;
-        }
-        traverse<C, LP, XT>(P.ix, P.a, P.gvis_words, Q, pool, W, vis);
-        if (A.stats && lane == 0) {
-            A.stats[qi * FROG_STAT_N + FROG_STAT_SCANROWS] = 0;
-            A.stats[qi * FROG_STAT_N + FROG_STAT_FALLBACK] = 0;
+        } else {
+            traverse<C, LP, XT>(P.ix, P.a, P.gvis_words, Q, pool, W, vis);
+            if (A.stats && lane == 0) {
+                A.stats[qi * FROG_STAT_N + FROG_STAT_SCANROWS] = 0;
+                A.stats[qi * FROG_STAT_N + FROG_STAT_FALLBACK] = 0;
+            }
         }
     }
 }

@@ -103,16 +103,6 @@ __device__ __forceinline__ int mbcnt(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// The values of the lanes in `mask`, moved to lanes 0 .. popc(mask) - 1 in
-// lane order (a forward permute: every lane sends its value to a distinct
-// lane, the others after the selected ones).
-__device__ __forceinline__ int32_t compact_lanes(int32_t v, uint64_t mask) {
-    const int lane = __lane_id();
-    const int below = mbcnt(mask);
-    const int dst = ((mask >> lane) & 1ull) ? below : __popcll(mask) + (lane - below);
-    return __builtin_amdgcn_ds_permute(dst << 2, v);
-}
-
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, int l) {
     uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, l);
     uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
@@ -1021,9 +1011,13 @@ __device__ void traverse_lean(const DevIndex& ix, const SearchLaunch& A, const Q
                         // a8; two steps, their loads in flight together, before
                         // their keys are inserted when more than 8 candidates
                         // are fresh (unclustered data leaves most of the
-                        // budget).  fp32 rows of 65 to 128 values: one step
-                        // at a time, two made one query alone 111 us instead
-                        // of 105.
+                        // budget).  fp32 rows of 65 to 128 values take one step
+                        // at a time: two are 1.02 to 1.17 times as fast on
+                        // unclustered rows, but 0.96 to 1.05 on clustered ones
+                        // (one query alone, 100k x 128: 83 us, 87 with two;
+                        // the wider queries and rows spill).  Shorter rows,
+                        // two against one: 1.02 to 1.16 unclustered, 0.98 to
+                        // 1.07 clustered.
                         if constexpr (C > 0 && (C <= 2 || sizeof(XT) == 2)) {
                             if (ns - j0 > 8) {
                                 const int32_t id1 = W.enbuf[j + 8 < ns ? j + 8 : ns - 1];

@@ -39,7 +39,8 @@ namespace frog {
 //   s_tile_kernel     tiles of 16 consecutive places: the span of their
 //                     pieces of the window
 //   s_small_kernel    (batches of at most kSmallQ queries) one workgroup in
-//                     place of the three before: the pairs sorted in LDS
+//                     place of the kernels before but s_plan_kernel: the pairs
+//                     sorted in LDS
 //   s_scan_kernel     one wavefront per (tile, chunk of its span): 16 x 16
 //                     blocks of q.x on the matrix cores, the approximate
 //                     squared distance |q|^2 + |x|^2 - 2 q.x of each query's
@@ -69,7 +70,11 @@ constexpr int kSFull = 32;       // buckets per window for pieces that cover it 
                                  // so that their atomic counters do not contend)
 constexpr int kSPer = 2 * kSSub + kSFull;   // buckets per window
 constexpr int kOffPer = 3;       // windows per thread of s_wscan_kernel (nwin <= 3072)
-constexpr int kSmallQ = 128;     // batches up to this size are planned by two kernels
+// batches up to this size are planned by two kernels: a thread of one
+// workgroup per pair (1,024).  Against six kernels, 200k x 128 and 20k x 32,
+// L = 32 and 64: 1 query 1.08 to 1.18 times as fast, 32 queries 1.04 to 1.11,
+// 128 queries 1.00 to 1.06.
+constexpr int kSmallQ = 128;
 constexpr int kQSub = 64;        // counters per class of the traversal's query order
 constexpr int kQLine = 32;       // their stride (one 128-byte line each: atomics on one line serialise)
 

@@ -320,8 +320,9 @@ __global__ __launch_bounds__(kBlock) void s_tile_kernel(SParams P) {
 // and scattered places), cuts each window's pairs into tiles of 16, builds the
 // tiles and sets the query order.  With the plan kernel before it this
 // replaces five of the six planning launches, each of which takes about 4.5
-// us however small the batch (12 queries: 139 -> 130 us per call; at 100
-// queries the sort takes what the launches did).
+// us however small the batch (12 queries of 200k x 128, entry cap 2560,
+// L = 32: 163 -> 148 us per call; at 128 queries the sort takes about what the
+// launches did).
 __global__ __launch_bounds__(1024) void s_small_kernel(SParams P) {
     __shared__ uint64_t key[kSmallQ * kSMaxWin];
     __shared__ int32_t head[kSmallQ * kSMaxWin];   // first sorted pair of each tile

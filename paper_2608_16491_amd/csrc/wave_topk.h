@@ -1,8 +1,7 @@
-// Per-query lists of the smallest (approximate distance, row) pairs, kept by
-// one wavefront in LDS.  The matrix-core scans (the brute force and the
-// shared entry sample of the search) offer each query's candidates of a
-// 16-row block to its list; a full list holds its largest value as the
-// threshold a candidate has to beat.
+// A list of the smallest (approximate distance, row) pairs of a stream, kept
+// by one wavefront in LDS: the pool kernel of the shared entry sample merges a
+// query's scan lists with it, the brute force's merge kernel cuts a query's
+// list to the entries it re-ranks.  (The two scans keep lists of their own.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -46,93 +45,8 @@ __device__ __forceinline__ void wave_minmax_u32(uint32_t& mn, uint32_t& mx) {
     mx = rmx;
 }
 
-__device__ __forceinline__ float wave_max_pos(float v, int& pos) {
-    // max over the wavefront with the lowest position among equals
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const float ov = __shfl_xor(v, o);
-        const int op = __shfl_xor(pos, o);
-        if (ov > v || (ov == v && op < pos)) { v = ov; pos = op; }
-    }
-    return v;
-}
-
-// A list of at most `cap` (approximate distance, row) pairs in LDS (cap a
-// multiple of 64) and its state, also in LDS: the number of entries, and once
-// the list is full, the value and slot of its largest entry (the threshold a
-// new candidate has to beat).  Every row offered to the list and not kept has
-// a value at or above the final threshold.
-struct TopList {
-    float* v;
-    int32_t* r;
-    int32_t* st;   // [0] fill, [1] threshold (float bits), [2] slot of the largest
-};
-
-__device__ __forceinline__ float list_threshold(const int32_t* st) { return __int_as_float(st[1]); }
-
-// recompute the largest entry of a full list (all lanes)
-__device__ __forceinline__ void list_refresh(const TopList& Lst, int cap, float& thr, int& mpos) {
-    const int lane = __lane_id();
-    float best = Lst.v[lane];
-    int pos = lane;
-    for (int j = 64 + lane; j < cap; j += 64)
-        if (Lst.v[j] > best) { best = Lst.v[j]; pos = j; }
-    best = wave_max_pos(best, pos);
-    thr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(best)));
-    mpos = __builtin_amdgcn_readfirstlane(pos);
-}
-
-// Offer the candidates held by the lanes of `group_mask` (value a, row rw in
-// each such lane) to the list.  Returns true if a candidate was dropped or an
-// entry evicted.
-static __device__ __noinline__ bool offer(TopList Lst, int cap, uint64_t group_mask, float a, int32_t rw) {
-    const int lane = __lane_id();
-    int f = __builtin_amdgcn_readfirstlane(Lst.st[0]);
-    float thr = __int_as_float(__builtin_amdgcn_readfirstlane(Lst.st[1]));
-    int mpos = __builtin_amdgcn_readfirstlane(Lst.st[2]);
-    bool dropped = false;
-    const int c = __popcll(group_mask);
-    if (f + c <= cap) {
-        // room for all: append in parallel
-        if ((group_mask >> lane) & 1) {
-            const int pos = f + __popcll(group_mask & ((1ull << lane) - 1));
-            Lst.v[pos] = a;
-            Lst.r[pos] = rw;
-        }
-        f += c;
-        list_sync();
-        if (f == cap) list_refresh(Lst, cap, thr, mpos);
-    } else {
-        for (uint64_t m = group_mask; m; m &= m - 1) {
-            const int src = __builtin_ctzll(m);
-            const float av = __shfl(a, src);
-            const int32_t rv = __shfl(rw, src);
-            if (f < cap) {
-                if (lane == 0) { Lst.v[f] = av; Lst.r[f] = rv; }
-                ++f;
-                list_sync();
-                if (f == cap) list_refresh(Lst, cap, thr, mpos);
-                continue;
-            }
-            dropped = true;   // av itself, or the entry it evicts
-            if (!(av < thr)) continue;
-            if (lane == 0) { Lst.v[mpos] = av; Lst.r[mpos] = rv; }
-            list_sync();
-            list_refresh(Lst, cap, thr, mpos);
-        }
-    }
-    if (lane == 0) {
-        Lst.st[0] = f;
-        Lst.st[1] = __float_as_int(thr);
-        Lst.st[2] = mpos;
-    }
-    list_sync();
-    return dropped;
-}
-
-// Buffered variant for long streams: up to 2K keys (orderable float bits of
-// the value << 32 | row) in LDS.  Candidates below the threshold are
-// appended; a buffer about to overflow is cut to its K smallest (K-th value
+// Up to 2K keys (orderable float bits of the value << 32 | row) in LDS.
+// Candidates below the threshold are appended; a buffer about to overflow is cut to its K smallest (K-th value
 // found by bisection over the value bits, kept entries compacted in place),
 // whose largest value becomes the threshold (+inf until the first cut).
 // Every candidate offered and not kept has a value at or above the final
@@ -165,7 +79,7 @@ __device__ __forceinline__ void buf_init(const BufList& B) {
 // leave no such x).  The bisection over the value bits stops at the first x
 // that qualifies (for the exact cut: exactly K entries at or below x), so it
 // rarely runs to a single value.  The new threshold is at or below the value
-// of every dropped entry.  K is 32, 48, 64, 128 or 256.
+// of every dropped entry.  K is 48 to 512.
 template <int K>
 __device__ __forceinline__ void buf_cut(const BufList& B, bool exact = true) {
     constexpr int R = (2 * K + 63) / 64;   // entries per lane (the last register partly)
