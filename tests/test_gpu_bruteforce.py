@@ -104,7 +104,8 @@ def test_bruteforce_uncertified_rows_are_exact(k):
 
 
 @pytest.mark.parametrize("n,d,nq,k", [(1, 5, 3, 4), (15, 32, 33, 10), (257, 33, 1, 33), (1536, 64, 32, 64), (1537, 96, 31, 65),
-                                      (24575, 20, 70, 10), (24576, 128, 65, 129), (24592, 130, 17, 1), (393216, 16, 40, 10)])
+                                      (24575, 20, 70, 10), (24576, 128, 65, 129), (24592, 130, 17, 1), (393216, 16, 40, 10),
+                                      (393472, 16, 40, 10)])
 def test_bruteforce_sampling_passes(n, d, nq, k):
     # sizes around those at which a further sampling pass is added (1,536 and
     # 24,576 and 393,216 rows at k <= 64; half a tile, a tile and a bit more

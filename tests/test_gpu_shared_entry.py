@@ -275,7 +275,10 @@ def test_shared_query_order_classes(tiny, kind):
 def test_shared_small_batches(nq):
     # batches up to 128 queries are planned by the one-workgroup kernel: sizes
     # around its wavefronts and powers of two of pairs, with empty, covered
-    # and wide ranges among them, and runs over up to 8 windows and more
+    # and wide ranges among them.  Runs meet 1 to 3 windows with caps of 600
+    # and 9,000; with a cap of 2,560 (windows of 1,024 positions) ranges just
+    # below twice the cap keep level 0, whose runs of 5,100 positions meet 5 or 6
+    # (more than 6 cannot be had: windows hold at least 2/5 of the cap)
     print(f"[gpu] shared entry sample: small batch nq={nq}", flush=True)
     w = workloads.make("tiny", n=12000, nq=nq)
     lo, hi = w.lo.copy(), w.hi.copy()
@@ -288,3 +291,14 @@ def test_shared_small_batches(nq):
         g_ids, g_d = c.gpu(10, 32, **p)
         o_ids, o_d, _ = c.cpu(10, 32, **p)
         assert_parity(g_ids, g_d, o_ids, o_d)
+    for i in (3, 4):
+        lo[i::5] = np.random.default_rng(i).integers(0, 12000 - 5100, len(lo[i::5]))
+        hi[i::5] = lo[i::5] + 5099
+    if nq >= 64:
+        met = (hi[3::5] // 1024 - lo[3::5] // 1024 + 1).astype(int)
+        assert met.min() >= 5 and met.max() == 6    # the attribute is a permutation: values are ranks
+    c = Case(w.X, w.attr, w.Q, lo, hi)
+    p = dict(SH, epn_max=2560)
+    g_ids, g_d = c.gpu(10, 32, **p)
+    o_ids, o_d, _ = c.cpu(10, 32, **p)
+    assert_parity(g_ids, g_d, o_ids, o_d)
